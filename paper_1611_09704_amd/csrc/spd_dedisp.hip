@@ -10,11 +10,15 @@
 // the output (float) holds them exactly (below 2^24 for the up to 65,536
 // channels a plan accepts).
 //
+// Lists whose neighbouring trials lie within a few samples of delay, the common
+// case, go to the matrix cores (dedisp_mfma_kernel below).  The kernels for any
+// other list:
+//
 // Kernel layout (gfx950).  A work-group owns 16 consecutive trials x 512
 // consecutive starts; each of its 4 waves owns 4 trials, and lane l the
 // starts t0 + l + 64k (k < 8).  Channels come in chunks of up to 16, staged
 // in LDS relative to g = (t0 + delay of the group's first trial) & ~3:
-//  * wide layout (dedisp_u8_wide_kernel, the common case): entry e is 16
+//  * wide layout (dedisp_u8_wide_kernel): entry e is 16
 //    bytes holding x[g + e + 64k], k < 8, as 16-bit fields, so one 16-byte
 //    LDS read gives a lane all 8 of its starts for a trial; the next chunk's
 //    bytes are loaded into registers while the current one accumulates;
@@ -36,10 +40,12 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
 #include "spd_abi_internal.h"
+#include "spd_device.h"
 
 namespace spd {
 namespace {
@@ -317,8 +323,249 @@ __global__ __launch_bounds__(64 * kDdWaves) void dedisp_u8_wide_kernel(DedispArg
     dd_store(a, d0, wv, lane, t0, tot);
 }
 
-// SPD_DEDISP_FORM=generic selects the chunk-by-chunk kernel for any plan (the
-// two kernels give identical sums).
+// ---------------------------------------------------------------------------
+// Matrix form (fine DM grids: 4 consecutive trials differ by at most 4 samples)
+// ---------------------------------------------------------------------------
+//
+// The sum over channels is a product with 0/1 matrices, which the matrix cores
+// evaluate exactly in 8-bit integers.  One product covers 4 consecutive trials
+// x 4 consecutive starts (its 16 rows), 16 columns of starts 16 apart, and 8
+// channels x 16 sample shifts (its 128 inner elements):
+//   row (trial i, phase j), column n:  y[4q+i][t + 16n + j]
+//     += sum over c, r of A[(i,j)][(c,r)] * x[c][w_c + 16n + r],
+//   A[(i,j)][(c,r)] = 1 iff r == j + t + D(4q+i, c) - w_c,
+// with w_c = t + D(4q, c) rounded down to 4 bytes, so r <= 3 + 3 + 4.  A has one
+// 1 in 16 elements, so it goes in as the structured-sparse operand
+// (v_smfmac_i32_16x16x128_i8: 2 of every 4 elements, 2 index bits each), which
+// doubles the channels per product.  The starts 4 further on are the same
+// bytes with A moved by 4 (r <= 14), so 24 bytes of a lane serve the 16
+// consecutive starts t + 16n ..: four products.
+//   B (samples): lane (n = l%16, g = l/16) holds 16 bytes of channel g, then 16
+//   of channel g + 4.  A: lane (row l%16, g = l/16) holds channels 2g and
+//   2g + 1, 8 bytes each: byte 2(r/4) is 1, every index field of the channel
+//   r%4.  Lane (n, g) ends with starts t + 16n .. of trial 4q + g.
+// Samples enter as x - 128 (xor 0x80: signed bytes) and every output gets
+// 128 * n_chan back; all sums are exact in 32 bits.
+//
+// A work-group owns 4*NW trials (a quad per wave) x 256*NS starts and walks the
+// channels 8 at a time, the bytes of the next 8 in flight.  In LDS each channel
+// has two copies, one dword apart, so that the reads, which start at any dword,
+// are aligned 8-byte reads (off their natural alignment they take 64 cycles
+// instead of 2.5); a channel sits an odd number of entries after the one
+// before, so that the 16-lane groups of a read use different banks.
+//
+// FAR (4 consecutive trials up to 9 samples apart): r may reach 15, so A is
+// never moved; every 4 starts take their own read, in the other copy.
+//
+// Measured (4,096 channels x 6,000 trials x 2^17 samples): 28.2 ms, 1.1e14 of the
+// definition's additions per second, against 97.6 ms for the wide layout, whose
+// LDS reads and vector adds cover 8 sums an instruction.  The products take
+// about half of it (22.5 cycles each, 1.52e9 of them); the rest is the staging's
+// vector work, which the products only partly hide (66 instructions a wave and 8
+// channels), and the LDS (53% busy).  Against the steps on the way: dense
+// products (4 channels) 33.4 ms; exact byte alignment through 8 copies, with 8
+// shifts a channel, 34.1 (the copies' LDS writes); 512 starts x 128 trials 33.0
+// dense (twice the matrix-A work a product).
+constexpr int kMfCh = 8;                    // channels per product and per LDS buffer
+constexpr int kMfSpan4 = 4, kMfSpan4Far = 9;   // most delay between trials 4q and 4q+3 (see FAR below)
+constexpr int kMfSpan = 120;                // most delay between the first trials of a work-group's quads
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef const __attribute__((address_space(3))) uint8_t LdsByte;
+typedef const __attribute__((address_space(3))) uint32_t LdsWord;
+typedef const volatile __attribute__((address_space(3))) u32x2 LdsPair;
+
+// A work-group's starts, the 8-byte entries of a copy read when its trials differ by at most `span`, and the
+// entries a copy has room for.
+__host__ __device__ constexpr int mf_starts(int ns) { return 256 * ns; }
+__host__ __device__ constexpr int mf_entries(int ns, int span, bool far)
+{
+    return ((3 + (far ? 4 : 0) + span) >> 3) + 32 * ns + 1;
+}
+__host__ __device__ constexpr int mf_copy(int ns) { return (mf_entries(ns, kMfSpan, true) + 15) & ~15; }
+// LDS bytes: a channel's two copies; one buffer with its table (4 bytes per trial and channel, quads 144 bytes
+// apart so that 16 of them use all banks).
+__host__ __device__ constexpr int mf_chan_bytes(int ns) { return 2 * 8 * mf_copy(ns) + 24; }
+__host__ __device__ constexpr int mf_buffer_bytes(int nw, int ns) { return kMfCh * mf_chan_bytes(ns) + nw * 144; }
+
+// Three dwords of a row from byte g on (a multiple of 4).  Dwords past the last whole one of the row, which only
+// reach starts past the last, repeat it; a row's last, partial dword is read byte by byte.
+__device__ inline void mf_load3(const uint8_t* row, int64_t g, int64_t n_samp, uint32_t (&D)[3])
+{
+    const int64_t whole = n_samp & ~(int64_t)3;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) D[k] = whole ? *(const uint32_t*)(row + min(g + 4 * k, whole - 4)) : 0u;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (g + 4 * k == whole && whole < n_samp) D[k] = dd_load4(row, whole, n_samp);
+}
+
+template <int NW, int NS, bool FAR>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4))) void dedisp_mfma_kernel(DedispArgs a)
+{
+    extern __shared__ __align__(16) uint8_t mf_smem[];
+    constexpr int NT = 4 * NW, TPC = 8 * NW;                // trials; threads staging one channel
+    constexpr int RND = (mf_copy(NS) + TPC - 1) / TPC;      // staging items per thread
+    constexpr int CB = 8 * mf_copy(NS), kTabAt = kMfCh * mf_chan_bytes(NS), kBuf = mf_buffer_bytes(NW, NS);
+    constexpr uint32_t kOdd = 0x8000;                       // table: the quad's bytes start in the second copy
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint64_t wg = xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t t0 = (int64_t)(wg / (uint32_t)a.n_dm_tiles) * mf_starts(NS);   // a multiple of 4
+    const int d0 = (int)(wg % (uint32_t)a.n_dm_tiles) * NT;
+    const int E = a.entries;
+    // thread (ch, i): entries of channel c0 + ch's copies and, i < NT, trial i's table entry there (the threads
+    // without one stage the first entries, so that they also have the last, partial round)
+    const int ch = tid / TPC, i0 = tid % TPC, e0 = (i0 + NT) % TPC;
+    const int chan_at = ch * mf_chan_bytes(NS);
+    const double dm0 = a.dm[d0], dmt = a.dm[min(d0 + i0, a.n_dm - 1)];
+    const bool interior = t0 + a.max_delay + 8 * E + 16 <= a.n_samp;
+    const int last = a.n_chan - 1;
+
+    // the next chunk: its samples, its first trial's delay and this thread's trial's
+    uint32_t D[RND][3];
+    int32_t base = 0, dly = 0;
+    double kc = a.kc[min(ch, last)];                        // loaded a chunk ahead
+    auto fetch = [&](int c0) {
+        const int c = min(c0 + ch, last);
+        base = dd_delay(dm0, kc);
+        if (i0 < NT) dly = dd_delay(dmt, kc);
+        const uint8_t* row = a.fb + (int64_t)c * a.stride;
+        const int64_t g0 = (t0 + base) & ~(int64_t)3;
+#pragma unroll
+        for (int r = 0; r < RND; ++r) {
+            const int i = e0 + TPC * r;
+            if (i >= E) break;
+            const int64_t g = g0 + 8 * i;
+            if (interior) {
+                struct __attribute__((aligned(4))) U3 { uint32_t v[3]; };
+                const U3 u = *(const U3*)(row + g);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) D[r][k] = u.v[k];
+            } else {
+                mf_load3(row, g, a.n_samp, D[r]);
+            }
+        }
+        kc = a.kc[min(c0 + kMfCh + ch, last)];
+    };
+    auto store = [&](uint8_t* buf, int c0) {
+        if (c0 + kMfCh > a.n_chan) {                        // channels past the last add nothing
+            const bool have = c0 + ch < a.n_chan;
+#pragma unroll
+            for (int r = 0; r < RND; ++r)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) D[r][k] = have ? D[r][k] : 0x80808080u;
+        }
+#pragma unroll
+        for (int r = 0; r < RND; ++r) {
+            const int i = e0 + TPC * r;
+            if (i >= E) break;
+            const u32x2 v0 = {D[r][0] ^ 0x80808080u, D[r][1] ^ 0x80808080u};
+            const u32x2 v1 = {v0.y, D[r][2] ^ 0x80808080u};
+            *(u32x2*)(buf + chan_at + 8 * i) = v0;
+            *(u32x2*)(buf + chan_at + CB + 8 * i) = v1;
+        }
+        if (i0 < NT) {
+            // per trial: the offset of its quad's bytes, and 4 * (its first phase's shift) in the high half
+            int32_t dq = __builtin_amdgcn_mov_dpp(dly, 0x00, 0xf, 0xf, true);      // quad_perm 0,0,0,0
+            asm("" : "+v"(dq));                             // keep the move by itself
+            const int p = (base & 3) + (dq - base);
+            const uint32_t odd = (p >> 2) & 1;
+            const uint32_t off = (uint32_t)(chan_at + (p & ~7)) + odd * (CB | kOdd);
+            const uint32_t r4 = (uint32_t)(4 * ((p & 3) + (dly - dq)));
+            *(uint32_t*)(buf + kTabAt + 144 * (i0 >> 2) + 16 * ch + 4 * (i0 & 3)) = off | (r4 << 16);
+        }
+    };
+
+    i32x4 acc[4 * NS] = {};
+    const int n = lane & 15, kb = lane >> 4;
+    auto multiply = [&](const uint8_t* buf) {
+        // table entries of this lane's trial (A's row) for channels g, g + 4 (B) and 2g, 2g + 1 (A)
+        LdsByte* tab = (LdsByte*)buf + kTabAt + 144 * wv + 4 * (n >> 2);
+        const uint32_t e0 = *(LdsWord*)(tab + 16 * kb), e1 = *(LdsWord*)(tab + 16 * kb + 64);
+        LdsByte* b0 = (LdsByte*)buf + (e0 & 0x7fff) + 16 * n;
+        LdsByte* b1 = (LdsByte*)buf + (e1 & 0x7fff) + 16 * n;
+        const uint32_t s0 = (*(LdsWord*)(tab + 32 * kb) >> 16) + 4 * (n & 3);        // 4r
+        const uint32_t s1 = (*(LdsWord*)(tab + 32 * kb + 16) >> 16) + 4 * (n & 3);
+        // 1 in byte 2(r/4): bit 16(r/4) = (4r & 48); A moved by 4: 16 bits higher
+        const uint64_t v0 = 1ull << (s0 & 48), v1 = 1ull << (s1 & 48);
+        const uint64_t w0 = v0 << 16, w1 = v1 << 16;
+        const i32x4 av = {(int)v0, (int)(v0 >> 32), (int)v1, (int)(v1 >> 32)};
+        const i32x4 aw = {(int)w0, (int)(w0 >> 32), (int)w1, (int)(w1 >> 32)};
+        const int ix = (int)((s0 >> 2 & 3) * 0x5555u + (s1 >> 2 & 3) * 0x55550000u);
+        // FAR: operand m is starts 256 (m/4) + 4 (m%4) + 16n ..; else starts 256 (m/2) + 8 (m%2) + 16n .., for
+        // two products.  It is read a step ahead, and the steps are kept apart (the scheduler would fold the
+        // reads into one register set and wait for each).
+        constexpr int kSteps = FAR ? 4 * NS : 2 * NS;
+        LdsByte* c0 = b0;
+        LdsByte* c1 = b1;
+        if (FAR) {                                          // 4 bytes on: the other copy
+            c0 += e0 & kOdd ? 8 - CB : CB;
+            c1 += e1 & kOdd ? 8 - CB : CB;
+        }
+        i32x8 bv[2];
+        auto read = [&](int m) {
+            // volatile: single 8-byte reads straight into the operand (paired by the compiler they take three
+            // times as long)
+            const int at = FAR ? 256 * (m >> 2) + 8 * (m >> 1 & 1) : 256 * (m >> 1) + 8 * (m & 1);
+            LdsByte* p = (FAR && (m & 1) ? c0 : b0) + at;
+            LdsByte* q = (FAR && (m & 1) ? c1 : b1) + at;
+            const u32x2 x0 = *(LdsPair*)p, x1 = *(LdsPair*)(p + 8);
+            const u32x2 y0 = *(LdsPair*)q, y1 = *(LdsPair*)(q + 8);
+            bv[m & 1] = i32x8{(int)x0.x, (int)x0.y, (int)x1.x, (int)x1.y, (int)y0.x, (int)y0.y, (int)y1.x, (int)y1.y};
+        };
+        read(0);
+#pragma unroll
+        for (int m = 0; m < kSteps; ++m) {
+            if (m + 1 < kSteps) read(m + 1);
+            if (FAR) {
+                acc[m] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(av, bv[m & 1], acc[m], ix, 0, 0);
+            } else {
+                acc[2 * m] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(av, bv[m & 1], acc[2 * m], ix, 0, 0);
+                acc[2 * m + 1] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(aw, bv[m & 1], acc[2 * m + 1], ix, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    fetch(0);
+    store(mf_smem, 0);
+    if (kMfCh < a.n_chan) fetch(kMfCh);
+    __syncthreads();
+    int cur = 0;
+    for (int c0 = 0; c0 < a.n_chan; c0 += kMfCh) {
+        const bool more = c0 + kMfCh < a.n_chan;
+        if (more) {
+            store(mf_smem + (cur ^ 1) * kBuf, c0 + kMfCh);
+            if (c0 + 2 * kMfCh < a.n_chan) fetch(c0 + 2 * kMfCh);
+        }
+        multiply(mf_smem + cur * kBuf);
+        __syncthreads();
+        cur ^= 1;
+    }
+
+    const int bias = 128 * a.n_chan;
+    const int d = d0 + 4 * wv + kb;
+    if (d >= a.n_dm) return;
+    float* orow = a.out + (int64_t)d * a.out_stride;
+#pragma unroll
+    for (int k = 0; k < 4 * NS; ++k) {
+        const int64_t t = t0 + 256 * (k >> 2) + 16 * n + 4 * (k & 3);
+        struct __attribute__((aligned(4))) F4 { float v[4]; } f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f.v[j] = (float)(acc[k][j] + bias);
+        if (t + 3 < a.n_out) {
+            *(F4*)(orow + t) = f;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (t + j < a.n_out) orow[t + j] = f.v[j];
+        }
+    }
+}
+
+// SPD_DEDISP_FORM=generic selects the chunk-by-chunk kernel for any plan (all
+// kernels give identical sums).
 bool dd_force_generic()
 {
     const char* e = getenv("SPD_DEDISP_FORM");
@@ -337,7 +584,9 @@ struct spd_dedisp_plan {
     double* d_dm = nullptr;
     double* d_kc = nullptr;
     int32_t max_delay = 0, span = 0, entries = 0, chunk = 0, groups = 0;
-    int device = 0;
+    int32_t mf_span[3] = {-1, -1, -1};       // matrix form with 4, 8, 16 waves: the bound on its trials' delays, -1: none
+    bool mf_far = false;
+    int device = 0, cus = 256;
 };
 
 extern "C" {
@@ -373,6 +622,17 @@ spd_status dd_prepare(const spd_band* band, const double* dm, int32_t n_dm, std:
     if (!(p < (double)SPD_MAX_DELAY)) return fail(SPD_E_UNSUPPORTED, "largest delay exceeds %d samples", SPD_MAX_DELAY);
     *max_delay = dd_delay(dm[n_dm - 1], kc[b.n_chan - 1]);
     return SPD_OK;
+}
+
+// A bound on the delay difference, at any channel, between two trials of the same group of `n` (the first and
+// last of each group differ by at most the floor of their FP64 difference plus one; the products' rounding is
+// below 1e-6 samples for delays up to SPD_MAX_DELAY).
+int64_t dd_span_bound(const std::vector<double>& dm, int n, double k_last)
+{
+    double most = 0.0;
+    for (size_t d = 0; d < dm.size(); d += (size_t)n)
+        most = std::max(most, (dm[std::min(d + (size_t)n, dm.size()) - 1] - dm[d]) * k_last);
+    return (int64_t)floor(most + 1e-6) + 1;
 }
 
 }  // namespace
@@ -428,12 +688,20 @@ spd_status spd_dedisp_plan_create(const spd_band* band, const double* dm, int32_
         if ((size_t)cc * per_chan <= kDdLdsMax) { P->chunk = cc; break; }
     // wide layout: the largest entry read is 3 + 63 + span
     P->groups = (67 + span + 3) / 4;
+    // matrix form: trials 4q .. 4q+3 near enough, and per work-group size the span that its LDS copies hold
+    const int64_t span4 = dd_span_bound(P->dm, 4, kc[b.n_chan - 1]);
+    P->mf_far = span4 > kMfSpan4;
+    for (int k = 0; k < 3; ++k) {
+        const int64_t sp = dd_span_bound(P->dm, 16 << k, kc[b.n_chan - 1]);
+        P->mf_span[k] = span4 <= kMfSpan4Far && sp <= kMfSpan ? (int32_t)sp : -1;
+    }
     if (!P->chunk) {
         delete P;
         return fail(SPD_E_UNSUPPORTED, "trials 16 apart differ by %d samples of delay; at most about %d fit the LDS",
                     span, (int)(kDdLdsMax / 4) - 460);
     }
     hipError_t e = hipGetDevice(&P->device);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&P->cus, hipDeviceAttributeMultiprocessorCount, P->device);
     if (e == hipSuccess) e = hipMalloc((void**)&P->d_dm, sizeof(double) * n_dm);
     if (e == hipSuccess) e = hipMalloc((void**)&P->d_kc, sizeof(double) * b.n_chan);
     if (e == hipSuccess) e = hipMemcpy(P->d_dm, P->dm.data(), sizeof(double) * n_dm, hipMemcpyHostToDevice);
@@ -449,6 +717,53 @@ spd_status spd_dedisp_plan_create(const spd_band* band, const double* dm, int32_
 }
 
 }  // extern "C"
+
+namespace {
+
+template <int NW, int NS>
+hipError_t launch_mfma_nw(const DedispArgs& a, bool far, uint32_t grid, hipStream_t s)
+{
+    const dim3 g(grid), b(64 * NW);
+    const size_t lds = 2 * mf_buffer_bytes(NW, NS);
+    if (far) hipLaunchKernelGGL((dedisp_mfma_kernel<NW, NS, true>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((dedisp_mfma_kernel<NW, NS, false>), g, b, lds, s, a);
+    return hipGetLastError();
+}
+
+// The matrix form's work-groups: 4 << k waves (16 << k trials) x 256 * ns starts; k = -1: none.
+struct MfShape { int k, ns; };
+
+// 64 trials x 1,024 starts amortise the staging best (4,096 channels x 6,000 trials x 2^17 samples: 28.2 ms
+// against 38.6 with 32 x 512 starts) while they give three quarters of the CUs a work-group (256 channels x 200
+// trials x 50,001 samples, 196 groups: 60 against 72 us); below that smaller groups keep more CUs busy (128
+// channels x 100 trials x 10,000 samples: 20 against 31 us; 512 x 64 x 20,000: 70 against 97).  The 64-trial
+// groups' span limit also sends coarse lists to the smaller ones (512 x 500 x 20,000, 2 samples a trial: 147 us
+// with 32 x 512 starts, 264 in the wide layout).
+MfShape mf_pick(const spd_dedisp_plan* plan, int64_t n_out)
+{
+    auto groups = [&](int k, int ns) {
+        return ((plan->n_dm + (16 << k) - 1) / (16 << k)) * ((n_out + mf_starts(ns) - 1) / mf_starts(ns));
+    };
+    MfShape f{-1, 2};
+    if (plan->mf_span[2] >= 0 && 4 * groups(2, 4) >= 3 * plan->cus) f = {2, 4};
+    else if (plan->mf_span[1] >= 0) f = {1, 2 * groups(1, 4) >= 3 * plan->cus ? 4 : 2};
+    else if (plan->mf_span[0] >= 0) f = {0, 2};
+    if (f.k >= 0 && (uint64_t)groups(f.k, f.ns) * (uint64_t)(256 << f.k) > kMaxGridItems) f.k = -1;
+    return f;
+}
+
+hipError_t launch_mfma(const spd_dedisp_plan* plan, DedispArgs a, MfShape f, hipStream_t s)
+{
+    const int nt = 16 << f.k;
+    a.n_dm_tiles = (a.n_dm + nt - 1) / nt;
+    a.entries = mf_entries(f.ns, plan->mf_span[f.k], plan->mf_far);
+    const uint32_t grid = (uint32_t)(a.n_dm_tiles * ((a.n_out + mf_starts(f.ns) - 1) / mf_starts(f.ns)));
+    if (f.k == 2) return launch_mfma_nw<16, 4>(a, plan->mf_far, grid, s);
+    if (f.k == 0) return launch_mfma_nw<4, 2>(a, plan->mf_far, grid, s);
+    return f.ns == 4 ? launch_mfma_nw<8, 4>(a, plan->mf_far, grid, s) : launch_mfma_nw<8, 2>(a, plan->mf_far, grid, s);
+}
+
+}  // namespace
 
 namespace spd {
 
@@ -533,6 +848,10 @@ spd_status spd_dedisperse(const spd_dedisp_plan* plan, const spd_plane* fb, floa
     a.groups = plan->groups;
     a.max_delay = plan->max_delay;
     const dim3 grid((uint32_t)(n_dm_tiles * n_t_tiles));
+    if (!dd_force_generic()) {
+        const MfShape f = mf_pick(plan, n_out);
+        if (f.k >= 0) return device_status(launch_mfma(plan, a, f, (hipStream_t)stream), "de-dispersion launch");
+    }
     const size_t wide_lds = (size_t)kDdMaxChunk * plan->groups * 64;
     if (!dd_force_generic() && kDdMaxChunk * plan->groups <= 64 * kDdWaves * kWideRounds && wide_lds <= kDdLdsMax)
         hipLaunchKernelGGL(dedisp_u8_wide_kernel, grid, dim3(64 * kDdWaves), wide_lds, (hipStream_t)stream, a);
