@@ -1573,12 +1573,16 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
 // Sec. 2.3 / Algorithm 1, streaming form of the short lists 1..n (n <= 16)
 // ---------------------------------------------------------------------------
 //
-// A wave owns a run of kStreamRun consecutive starts of one row and walks it
-// in steps of kStreamStep.  Lane l takes the 4 consecutive starts 4l..4l+3 of
-// a step (block 0) and 256+4l..256+4l+3 (block 1), so its outputs are one
-// 16-byte SNR store and one 4-byte width-index store per block, and a store
-// instruction of the wave covers consecutive addresses.  A block needs the
-// samples 4l .. 4l+n+2 of its step: five aligned 16-byte LDS reads.
+// A row's starts are cut into steps of kStreamStep, on a grid that puts the
+// outputs of every step on a 64-byte boundary whatever the row's offset
+// (stream_origin: the first step begins up to 15 starts before the row).  A
+// wave owns a run of consecutive steps of one row.  Lane l takes the 4
+// consecutive starts 4l..4l+3 of a step (block 0) and 256+4l..256+4l+3 (block
+// 1), so its outputs are one aligned 16-byte SNR store and one 4-byte
+// width-index store per block, and a store instruction of the wave covers
+// consecutive addresses.  The samples are loaded 4 at a time at whatever
+// alignment that leaves them.  A block needs the samples 4l .. 4l+n+2 of its
+// step: five aligned 16-byte LDS reads.
 //
 // The wave's LDS holds two buffers of kStreamBuf floats: x' = x - mean of one
 // step and the first 16 samples of the next.  While a step is evaluated the
@@ -1595,32 +1599,44 @@ template <> struct RawT<SPD_F32> { using T = f32x4; };
 template <> struct RawT<SPD_F16> { using T = u32x2; };
 template <> struct RawT<SPD_U8> { using T = uint32_t; };
 
-// Four samples from column c as stored; past the end of the row the value is
-// unspecified (those samples only reach windows that start past the last
-// valid start).  `vec`: the row allows aligned vector loads at c.
+// The same types at the alignment of one element: a plain vector load at any
+// element offset (global memory takes them unaligned).
+template <int DT> struct RawAny;
+template <> struct RawAny<SPD_F32> { typedef f32x4 T __attribute__((aligned(4))); };
+template <> struct RawAny<SPD_F16> { typedef u32x2 T __attribute__((aligned(2))); };
+template <> struct RawAny<SPD_U8> { typedef uint32_t T __attribute__((aligned(1))); };
+
 template <int DT>
-__device__ __forceinline__ typename RawT<DT>::T raw4(const Loader<DT>& ld, int64_t c, int64_t ncols, bool vec)
+__device__ __forceinline__ typename RawT<DT>::T raw4_any(const Loader<DT>& ld, int64_t c)
 {
-    using T = typename RawT<DT>::T;
-    if (vec && c + 3 < ncols) return *(const T*)(ld.row + c);
+    return __builtin_nontemporal_load((const typename RawAny<DT>::T*)(ld.row + c));   // read once
+}
+
+// Four samples from column c as stored; outside the row the value is
+// unspecified (those samples only reach windows that start outside the valid
+// starts).
+template <int DT>
+__device__ __forceinline__ typename RawT<DT>::T raw4(const Loader<DT>& ld, int64_t c, int64_t ncols)
+{
+    auto in = [&](int k) { return c + k >= 0 && c + k < ncols; };
     if constexpr (DT == SPD_F32) {
         f32x4 v;
-        v.x = c < ncols ? ld.row[c] : 0.f;
-        v.y = c + 1 < ncols ? ld.row[c + 1] : 0.f;
-        v.z = c + 2 < ncols ? ld.row[c + 2] : 0.f;
-        v.w = c + 3 < ncols ? ld.row[c + 3] : 0.f;
+        v.x = in(0) ? ld.row[c] : 0.f;
+        v.y = in(1) ? ld.row[c + 1] : 0.f;
+        v.z = in(2) ? ld.row[c + 2] : 0.f;
+        v.w = in(3) ? ld.row[c + 3] : 0.f;
         return v;
     } else if constexpr (DT == SPD_F16) {
         const uint16_t* h = (const uint16_t*)ld.row;
         uint32_t e[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) e[k] = c + k < ncols ? (uint32_t)h[c + k] : 0u;
+        for (int k = 0; k < 4; ++k) e[k] = in(k) ? (uint32_t)h[c + k] : 0u;
         const u32x2 u = {e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
         return u;
     } else {
         uint32_t u = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) u |= (c + k < ncols ? (uint32_t)ld.row[c + k] : 0u) << (8 * k);
+        for (int k = 0; k < 4; ++k) u |= (in(k) ? (uint32_t)ld.row[c + k] : 0u) << (8 * k);
         return u;
     }
 }
@@ -1677,15 +1693,15 @@ __device__ __forceinline__ void short_block(const float* src, const float (&a)[N
 }
 
 // One candidate per (start, lane) with snr >= threshold among the lane's
-// `cnt` starts beginning at t: one ballot per start index, one atomic per
+// starts t + i, lo <= i < cnt: one ballot per start index, one atomic per
 // wave and start index that has candidates.
 __device__ __forceinline__ void emit_block_cands(const BoxcarArgs& ba, const WidthPlan& wp, int64_t r, int64_t t,
-                                                 int cnt, const float (&sv)[4], uint32_t packed)
+                                                 int lo, int cnt, const float (&sv)[4], uint32_t packed)
 {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const bool pred = i < cnt && sv[i] >= ba.threshold;
+        const bool pred = i >= lo && i < cnt && sv[i] >= ba.threshold;
         const uint64_t mask = __ballot(pred);
         if (!mask) continue;
         const int cntw = __popcll(mask);
@@ -1725,36 +1741,50 @@ __device__ __forceinline__ void short_coefs(const spd_row_stats& st, float (&a)[
     for (int j = 0; j < N; ++j) a[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cf), j));
 }
 
-// One run of kStreamRun starts at t_begin whose every start is valid and
-// every sample it reads (its starts plus the 16 samples after them) lies
-// inside a row that allows vector loads.  OUT: both outputs are written with
-// 16-byte and 4-byte stores; otherwise candidates only.  Every step is whole,
-// so the stores are unconditional and a step's loads are waited for without
-// waiting for the previous step's stores.
+// How far the outputs of (row r, start 0) lie past a 64-byte boundary of the
+// SNR array (or 16-byte boundary of the width indices), in starts.
+__device__ __forceinline__ int stream_origin(const BoxcarArgs& ba, int64_t r)
+{
+    const uint64_t at = (uint64_t)(r * ba.out_stride) +
+                        (ba.snr ? (uint64_t)(uintptr_t)ba.snr / 4 : (uint64_t)(uintptr_t)ba.widx);
+    return ba.snr || ba.widx ? (int)(at & 15) : 0;
+}
+
+// One run of S steps at t_begin whose every start is valid and every sample it
+// reads (its starts plus the 16 samples after them) lies inside the row.
+// OUT: both outputs are written with 16-byte and 4-byte stores; otherwise
+// candidates only.  Every step is whole, so the stores are unconditional and a
+// step's loads are waited for without waiting for the previous step's stores.
 template <int DT, int N, bool OUT>
-__device__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, int64_t t_begin, const spd_row_stats& st,
-                                const BoxcarArgs& ba, const WidthPlan& wp, float* buf)
+__device__ __forceinline__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, int64_t t_begin, const spd_row_stats& st,
+                                                const BoxcarArgs& ba, const WidthPlan& wp, float* buf)
 {
     using Raw = typename RawT<DT>::T;
-    constexpr int S = kStreamSteps;
+    const int S = ba.steps;
     const int lane = threadIdx.x & 63, lo = 4 * lane;
     float a[N];
     short_coefs<N>(st, a);
     const float mu_hi = (float)st.mean;
     const float mu_lo = (float)(st.mean - (double)mu_hi);
     const Loader<DT> ld(pl, r);
-    const Raw* rowp = (const Raw*)(ld.row + t_begin) + lane;      // one Raw per 4 samples
+    const int64_t c = t_begin + lo;
     float* so = OUT ? ba.snr + r * ba.out_stride + t_begin + lo : nullptr;
     uint8_t* wo = OUT ? ba.widx + r * ba.out_stride + t_begin + lo : nullptr;
 
     float* A = buf;
     float* Bv = buf + kStreamBuf;
     {
-        const Raw s0 = rowp[0], s1 = rowp[64];
+        const Raw s0 = raw4_any<DT>(ld, c), s1 = raw4_any<DT>(ld, c + 256);
         put_shifted(A + lo, cvt4<DT>(ld, s0), mu_hi, mu_lo);
         put_shifted(A + 256 + lo, cvt4<DT>(ld, s1), mu_hi, mu_lo);
     }
-    Raw r0 = rowp[kStreamStep / 4], r1 = rowp[kStreamStep / 4 + 64];
+    Raw r0{}, r1{};
+    if (S > 1) {
+        r0 = raw4_any<DT>(ld, c + kStreamStep);
+        r1 = raw4_any<DT>(ld, c + kStreamStep + 256);
+    } else if (lane < 4) {
+        r0 = raw4_any<DT>(ld, c + kStreamStep);
+    }
     if (lane < 4) put_shifted(A + kStreamStep + lo, cvt4<DT>(ld, r0), mu_hi, mu_lo);
     wave_sync();
     for (int k = 0; k < S; ++k) {
@@ -1762,12 +1792,12 @@ __device__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, int64_t t_begin, 
             put_shifted(Bv + lo, cvt4<DT>(ld, r0), mu_hi, mu_lo);
             put_shifted(Bv + 256 + lo, cvt4<DT>(ld, r1), mu_hi, mu_lo);
         }
-        const Raw* nx = rowp + (k + 2) * (kStreamStep / 4);
-        if (k + 2 < S) {                                    // read once: nontemporal
-            r0 = __builtin_nontemporal_load(nx);
-            r1 = __builtin_nontemporal_load(nx + 64);
+        const int64_t nx = c + (k + 2) * kStreamStep;
+        if (k + 2 < S) {
+            r0 = raw4_any<DT>(ld, nx);
+            r1 = raw4_any<DT>(ld, nx + 256);
         } else if (k + 2 == S && lane < 4) {
-            r0 = nx[0];
+            r0 = raw4_any<DT>(ld, nx);
         }
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {
@@ -1776,7 +1806,7 @@ __device__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, int64_t t_begin, 
             short_block<N>(A + 256 * blk + lo, a, sv, pk);
             const int off = k * kStreamStep + 256 * blk;
             if (ba.cand && __ballot(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])) >= ba.threshold))
-                emit_block_cands(ba, wp, r, t_begin + off + lo, 4, sv, pk);
+                emit_block_cands(ba, wp, r, t_begin + off + lo, 0, 4, sv, pk);
             if (OUT) {                                                  // written once, never read here
                 const f32x4 q = {sv[0], sv[1], sv[2], sv[3]};
                 __builtin_nontemporal_store(q, (f32x4*)(so + off));
@@ -1789,18 +1819,19 @@ __device__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, int64_t t_begin, 
     }
 }
 
-// Starts [t_begin, min(t_begin + kStreamRun, nout)) of row r by one wave, for
-// any run: loads checked against the row end and against vector alignment,
-// stores per element where a step is partial or the rows do not allow vector
-// stores.  buf is the wave's 2*kStreamBuf floats of LDS (16-byte aligned).
+// Any run: the valid starts among S steps from t_begin (which may lie before
+// the row) of row r by one wave.  Steps inside the row load 4 samples at a
+// time, others are checked sample by sample; whole steps store vectors where
+// the outputs allow it, others per element.  buf is the wave's 2*kStreamBuf
+// floats of LDS (16-byte aligned).
 template <int DT, int N>
-__device__ void boxcar_run_short(const PlaneArg& pl, bool vec, int64_t r, int64_t t_begin, const spd_row_stats& st,
-                                 const BoxcarArgs& ba, const WidthPlan& wp, float* buf)
+__device__ __forceinline__ void boxcar_run_short(const PlaneArg& pl, int64_t r, int64_t t_begin, const spd_row_stats& st,
+                                                 const BoxcarArgs& ba, const WidthPlan& wp, float* buf)
 {
     using Raw = typename RawT<DT>::T;
     const int lane = threadIdx.x & 63;
     const int64_t nout = ba.nout;
-    const int64_t t_end = min(t_begin + kStreamRun, nout);
+    const int64_t t_end = min(t_begin + (int64_t)ba.steps * kStreamStep, nout);
     const int steps = (int)((t_end - t_begin + kStreamStep - 1) / kStreamStep);
     float a[N];
     short_coefs<N>(st, a);
@@ -1809,28 +1840,32 @@ __device__ void boxcar_run_short(const PlaneArg& pl, bool vec, int64_t r, int64_
     const Loader<DT> ld(pl, r);
     const int64_t ncols = pl.n_cols;
     const int lo = 4 * lane;
-    auto load = [&](int64_t off) -> Raw { return raw4<DT>(ld, t_begin + off, ncols, vec); };
+    auto load = [&](int step, int at) -> Raw {              // at: 0 or 256
+        const int64_t t = t_begin + (int64_t)step * kStreamStep;
+        if (t >= 0 && t + kStreamStep <= ncols) return raw4_any<DT>(ld, t + at + lo);   // uniform
+        return raw4<DT>(ld, t + at + lo, ncols);
+    };
 
     float* A = buf;
     float* Bv = buf + kStreamBuf;
     {
-        const Raw s0 = load(lo), s1 = load(lo + 256);
+        const Raw s0 = load(0, 0), s1 = load(0, 256);
         put_shifted(A + lo, cvt4<DT>(ld, s0), mu_hi, mu_lo);
         put_shifted(A + 256 + lo, cvt4<DT>(ld, s1), mu_hi, mu_lo);
     }
     Raw r0{}, r1{};
     if (steps > 1) {
-        r0 = load(kStreamStep + lo);
-        r1 = load(kStreamStep + 256 + lo);
+        r0 = load(1, 0);
+        r1 = load(1, 256);
     } else if (lane < 4) {
-        r0 = load(kStreamStep + lo);
+        r0 = load(1, 0);
     }
     if (lane < 4) put_shifted(A + kStreamStep + lo, cvt4<DT>(ld, r0), mu_hi, mu_lo);
     wave_sync();
 
     float* so = ba.snr ? ba.snr + r * ba.out_stride + t_begin : nullptr;
     uint8_t* wo = ba.widx ? ba.widx + r * ba.out_stride + t_begin : nullptr;
-    const bool vs = (ba.out_vec & 1u) != 0, vw = (ba.out_vec & 4u) != 0;
+    const bool vs = ((uintptr_t)so & 15) == 0, vw = ((uintptr_t)wo & 3) == 0;
     for (int k = 0; k < steps; ++k) {
         const int ks = k * kStreamStep;
         if (k + 1 < steps) {
@@ -1838,38 +1873,39 @@ __device__ void boxcar_run_short(const PlaneArg& pl, bool vec, int64_t r, int64_
             put_shifted(Bv + 256 + lo, cvt4<DT>(ld, r1), mu_hi, mu_lo);
         }
         if (k + 2 < steps) {
-            r0 = load(ks + 2 * kStreamStep + lo);
-            r1 = load(ks + 2 * kStreamStep + 256 + lo);
+            r0 = load(k + 2, 0);
+            r1 = load(k + 2, 256);
         } else if (k + 2 == steps && lane < 4) {
-            r0 = load(ks + 2 * kStreamStep + lo);
+            r0 = load(k + 2, 0);
         }
-        const bool whole = t_begin + ks + kStreamStep <= t_end;
+        const bool whole = t_begin + ks >= 0 && t_begin + ks + kStreamStep <= t_end;
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {
             float sv[4];
             uint32_t pk;
             short_block<N>(A + 256 * blk + lo, a, sv, pk);
             const int off = ks + 256 * blk + lo;
-            int cnt = 4;
+            int first = 0, cnt = 4;
             if (!whole) {
-                const int64_t left = t_end - (t_begin + off);
+                const int64_t t = t_begin + off, left = t_end - t;
+                first = t < 0 ? (int)min(-t, (int64_t)4) : 0;
                 cnt = left <= 0 ? 0 : (left >= 4 ? 4 : (int)left);
             }
             if (ba.cand && __ballot(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])) >= ba.threshold))
-                emit_block_cands(ba, wp, r, t_begin + off, cnt, sv, pk);
+                emit_block_cands(ba, wp, r, t_begin + off, first, cnt, sv, pk);
             if (whole && vs && so) {
                 *(float4*)(so + off) = make_float4(sv[0], sv[1], sv[2], sv[3]);
             } else if (so) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (i < cnt) so[off + i] = sv[i];
+                    if (i >= first && i < cnt) so[off + i] = sv[i];
             }
             if (whole && vw && wo) {
                 *(uint32_t*)(wo + off) = pk;
             } else if (wo) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (i < cnt) wo[off + i] = (uint8_t)(pk >> (8 * i));
+                    if (i >= first && i < cnt) wo[off + i] = (uint8_t)(pk >> (8 * i));
             }
         }
         if (k + 1 < steps && lane < 4) put_shifted(Bv + kStreamStep + lo, cvt4<DT>(ld, r0), mu_hi, mu_lo);

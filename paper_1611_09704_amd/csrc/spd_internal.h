@@ -20,13 +20,13 @@ constexpr int kWinX = 8;           // consecutive starts per lane in the registe
 constexpr int kSelCols = 4096;     // columns per work-group of the standalone threshold (16 per lane)
 constexpr int kWinTableFloats = (kMaxWidthsPadded + 2 * kMaxGroups + 63) / 64 * 64;
 
-// Streaming form of the short lists 1..n (n <= 16): a wave walks a run of
-// kStreamSteps steps of kStreamStep consecutive starts of one row; lane l
+// Streaming form of the short lists 1..n (n <= 16): a wave walks a run of a
+// few steps of kStreamStep consecutive starts of one row; lane l
 // takes starts 4l..4l+3 and 256+4l..256+4l+3 of each step.  Its LDS holds two
 // buffers of one step's samples plus the next 16.
 constexpr int kStreamStep = 512;
-constexpr int kStreamSteps = 16;
-constexpr int64_t kStreamRun = (int64_t)kStreamStep * kStreamSteps;
+constexpr int kStreamSteps = 8;         // of an ordinary launch; doubled where the grid would not hold the runs
+constexpr int kStreamStepsMax = 16;
 constexpr int kStreamBuf = kStreamStep + 16;
 
 // Register-window form: logical element m of a wave's LDS array is stored at
@@ -102,10 +102,8 @@ struct BoxcarArgs {
     int64_t* cand_count;
     float threshold;
     uint32_t beam;          // stored in each candidate (batched runs)
-    uint32_t out_vec;       // bit 0: snr rows allow 16-byte stores; bit 1: widx rows allow 8-byte stores;
-                            // bit 2: widx rows allow 4-byte stores
-    uint32_t reserved;
-    int64_t run0, run1;     // streaming form: the runs [run0, run1) of every row this launch covers
+    uint32_t out_vec;       // bit 0: snr rows allow 16-byte stores; bit 1: widx rows allow 8-byte stores
+    int32_t steps;          // streaming form: steps per run
 };
 
 struct SelectArgs {
