@@ -162,6 +162,9 @@ static void plan_window(const int* W, int n, bool unit, int X, size_t lds_cap, W
         wp.gstep[g] = (uint8_t)d;
     }
     wp.win = kind;
+    wp.win_unit = kind == 1;
+    for (int g = 0; g < (kind == 1 ? n / kGroup : 0); ++g)
+        if (wp.gstep[g] != 1) wp.win_unit = 0;
     wp.n_arr = n_arr;
     ba.npw = npp;
     ba.wave_floats = wave_floats;

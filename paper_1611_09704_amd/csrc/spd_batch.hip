@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UNIT ? 5 : 
 // The register-window form of the same grid launch (8 consecutive starts per
 // lane; tiles numbered for that form).  Capped at 128 VGPRs like the one-plane
 // kernel of the same form.
-template <int DT, int SMALLN>
+template <int DT, int SMALLN, bool UNIT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SMALLN == 0 ? 4 : 6))) void batch_boxcar_win_grid_kernel(
     const BeamDesc* beams, int n_beams, const spd_row_stats* stats, BoxcarArgs ba, WidthPlan wp)
 {
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SMALLN == 0
     ba.nout = d.nout;
     ba.beam = (uint32_t)b;
     const spd_row_stats st = stats[d.unit_start + r];
-    boxcar_tile_win<DT, SMALLN>(d.pl, d.vec != 0, r, tt, st, ba, wp, smem);
+    boxcar_tile_win<DT, SMALLN, false, UNIT>(d.pl, d.vec != 0, r, tt, st, ba, wp, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -302,7 +302,10 @@ static hipError_t enqueue_boxcar_win(spd_batch_plan* P, const Schedule& sc, cons
     const size_t lds = boxcar_lds_bytes(sc.waves, P->ba[2], true);
     if (total <= 0) return hipSuccess;
     if ((uint64_t)total * 64u * (uint64_t)sc.waves > kMaxGridItems) return hipErrorInvalidConfiguration;
-    if (wp.win == 1)
+    if (wp.win == 1 && wp.win_unit)
+        hipLaunchKernelGGL((batch_boxcar_win_grid_kernel<DT, 0, true>), dim3((unsigned)total), dim3(64 * sc.waves), lds,
+                           s, P->d_beams[2], P->n_beams, P->d_stats, ba, wp);
+    else if (wp.win == 1)
         hipLaunchKernelGGL((batch_boxcar_win_grid_kernel<DT, 0>), dim3((unsigned)total), dim3(64 * sc.waves), lds, s,
                            P->d_beams[2], P->n_beams, P->d_stats, ba, wp);
     else if (wp.n <= 8)

@@ -1148,6 +1148,78 @@ __device__ __forceinline__ double key_max(double a, double b)
 }
 
 // ---------------------------------------------------------------------------
+// raw loads, four samples at a time
+// ---------------------------------------------------------------------------
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+template <int DT> struct RawT;
+template <> struct RawT<SPD_F32> { using T = f32x4; };
+template <> struct RawT<SPD_F16> { using T = u32x2; };
+template <> struct RawT<SPD_U8> { using T = uint32_t; };
+
+// The same types at the alignment of one element: a plain vector load at any
+// element offset (global memory takes them unaligned).
+template <int DT> struct RawAny;
+template <> struct RawAny<SPD_F32> { typedef f32x4 T __attribute__((aligned(4))); };
+template <> struct RawAny<SPD_F16> { typedef u32x2 T __attribute__((aligned(2))); };
+template <> struct RawAny<SPD_U8> { typedef uint32_t T __attribute__((aligned(1))); };
+
+// STREAM: read once (nontemporal).
+template <int DT, bool STREAM = false>
+__device__ __forceinline__ typename RawT<DT>::T raw4_any(const Loader<DT>& ld, int64_t c)
+{
+    const typename RawAny<DT>::T* p = (const typename RawAny<DT>::T*)(ld.row + c);
+    if constexpr (STREAM) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+// Four samples from column c as stored; outside the row the value is
+// unspecified (those samples only reach windows that start outside the valid
+// starts).
+template <int DT>
+__device__ __forceinline__ typename RawT<DT>::T raw4(const Loader<DT>& ld, int64_t c, int64_t ncols)
+{
+    auto in = [&](int k) { return c + k >= 0 && c + k < ncols; };
+    if constexpr (DT == SPD_F32) {
+        f32x4 v;
+        v.x = in(0) ? ld.row[c] : 0.f;
+        v.y = in(1) ? ld.row[c + 1] : 0.f;
+        v.z = in(2) ? ld.row[c + 2] : 0.f;
+        v.w = in(3) ? ld.row[c + 3] : 0.f;
+        return v;
+    } else if constexpr (DT == SPD_F16) {
+        const uint16_t* h = (const uint16_t*)ld.row;
+        uint32_t e[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) e[k] = in(k) ? (uint32_t)h[c + k] : 0u;
+        const u32x2 u = {e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
+        return u;
+    } else {
+        uint32_t u = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u |= (in(k) ? (uint32_t)ld.row[c + k] : 0u) << (8 * k);
+        return u;
+    }
+}
+
+template <int DT>
+__device__ __forceinline__ float4 cvt4(const Loader<DT>& ld, typename RawT<DT>::T u)
+{
+    if constexpr (DT == SPD_F32) {
+        return make_float4(u.x, u.y, u.z, u.w);
+    } else if constexpr (DT == SPD_F16) {
+        const uint32_t lo = u.x, hi = u.y;
+        const float2 a = __half22float2(*reinterpret_cast<const __half2*>(&lo));
+        const float2 b = __half22float2(*reinterpret_cast<const __half2*>(&hi));
+        return make_float4(a.x, a.y, b.x, b.y);
+    } else {
+        return make_float4(ld.deq(u & 255u), ld.deq((u >> 8) & 255u), ld.deq((u >> 16) & 255u), ld.deq(u >> 24));
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Sec. 2.3 / Algorithm 1, register-window form
 // ---------------------------------------------------------------------------
 //
@@ -1162,8 +1234,11 @@ __device__ __forceinline__ double key_max(double a, double b)
 // D[t_i + o + d*j] at m = i + d*j.  The same holds for the list 1..n
 // (n <= 16) over x' itself.  Results are those of boxcar_tile: the same
 // running sums in the same order, and the same first-maximiser rule.
+// UNIT: every group steps by 1 (the lists 1..8k), so no step is chosen per
+// group and the winner's sums are remade from one read per width, not two
+// (79 VGPRs instead of 128: 6 waves per SIMD instead of 4).
 
-template <int DT, int SMALLN, bool DIT = false>
+template <int DT, int SMALLN, bool DIT = false, bool UNIT = false>
 __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t tt, const spd_row_stats& st,
                                 const BoxcarArgs& ba, const WidthPlan& wp, float* smem)
 {
@@ -1176,6 +1251,16 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
     const int64_t tw = tt * (int64_t)(nwaves * 64 * X) + (int64_t)wave * 64 * X;
     const int rows9 = ba.npw / 9;                                   // rows of 8 logical floats per array
     const int nlog = rows9 * 8;
+
+    // window inside the row (all but the last tiles): its first 1,024 samples are in flight while the tables are
+    // made, four vector loads per lane at whatever alignment the row has; lanes past the window reload its last
+    // four samples and skip the write
+    Loader<DT> ld(pl, r);
+    const bool inside = tw + nlog <= pl.n_cols;
+    typename RawT<DT>::T pre[4];
+    if (inside)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) pre[m] = raw4_any<DT>(ld, tw + min(4 * lane + 256 * m, nlog - 4));
 
     {
         const bool zero_var = (st.flags & SPD_FLAG_ZERO_VAR) != 0;
@@ -1197,24 +1282,21 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
     const float mu_lo = (float)(st.mean - (double)mu_hi);
 
     // stage x' = x - mean (array 0); zero beyond the row
-    Loader<DT> ld(pl, r);
-    if (vec && tw + nlog <= pl.n_cols) {
-        // window inside the row (all but the last tiles): four vector loads per
-        // lane in flight before any is written; lanes past the window reload
-        // its last four samples and skip the write
+    if (inside) {
         for (int k0 = 4 * lane; k0 < nlog; k0 += 1024) {
-            float4 v[4];
+            if (k0 >= 1024)
 #pragma unroll
-            for (int m = 0; m < 4; ++m) v[m] = ld.vec(tw + min(k0 + 256 * m, nlog - 4));
+                for (int m = 0; m < 4; ++m) pre[m] = raw4_any<DT>(ld, tw + min(k0 + 256 * m, nlog - 4));
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 const int k = k0 + 256 * m;
                 if (k < nlog) {
+                    const float4 v = cvt4<DT>(ld, pre[m]);
                     float* d = arrs + win_phys(k);                  // k..k+3 share one row of 9
-                    d[0] = (v[m].x - mu_hi) - mu_lo;
-                    d[1] = (v[m].y - mu_hi) - mu_lo;
-                    d[2] = (v[m].z - mu_hi) - mu_lo;
-                    d[3] = (v[m].w - mu_hi) - mu_lo;
+                    d[0] = (v.x - mu_hi) - mu_lo;
+                    d[1] = (v.y - mu_hi) - mu_lo;
+                    d[2] = (v.z - mu_hi) - mu_lo;
+                    d[3] = (v.w - mu_hi) - mu_lo;
                 }
             }
         }
@@ -1429,10 +1511,10 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
         // runs of groups with one step; two groups per trip let the carried
         // sums and maxima alternate registers instead of being copied
         for (int g = 0; g < ng;) {
-            const int d = wp.gstep[g];
-            int g1 = g + 1;
+            const int d = UNIT ? 1 : wp.gstep[g];
+            int g1 = UNIT ? ng : g + 1;
             while (g1 < ng && wp.gstep[g1] == d) ++g1;
-            if (d == 1) {
+            if (UNIT || d == 1) {
 #pragma unroll 2
                 for (; g < g1; ++g) group(std::integral_constant<int, 1>(), g);
             } else {
@@ -1447,7 +1529,7 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
         for (int i = 0; i < X; ++i) {
             const int g = gi[i];
             const float* gb = lb + tgb[g];
-            const bool two = tgs[g] == 2u;
+            const bool two = !UNIT && tgs[g] == 2u;
             const float4 c03 = *(const float4*)(coef + g * kGroup);
             const float4 c47 = *(const float4*)(coef + g * kGroup + 4);
             const float cf[8] = {c03.x, c03.y, c03.z, c03.w, c47.x, c47.y, c47.z, c47.w};
@@ -1455,8 +1537,12 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
             float s[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float d1 = gb[win_phys(i + j)], d2 = gb[win_phys(i + 2 * j)];
-                b = __fadd_rn(b, two ? d2 : d1);
+                float d = gb[win_phys(i + j)];
+                if (!UNIT && j) {
+                    const float d2 = gb[win_phys(i + 2 * j)];
+                    d = two ? d2 : d;
+                }
+                b = __fadd_rn(b, d);
                 s[j] = __fmul_rn(b, cf[j]);
             }
             int jj = -1;
@@ -1591,71 +1677,6 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
 // no work-group barrier is needed and every sample is read from HBM once.
 // The coefficients 1/sigma_w are wave-uniform (scalar registers).
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-template <int DT> struct RawT;
-template <> struct RawT<SPD_F32> { using T = f32x4; };
-template <> struct RawT<SPD_F16> { using T = u32x2; };
-template <> struct RawT<SPD_U8> { using T = uint32_t; };
-
-// The same types at the alignment of one element: a plain vector load at any
-// element offset (global memory takes them unaligned).
-template <int DT> struct RawAny;
-template <> struct RawAny<SPD_F32> { typedef f32x4 T __attribute__((aligned(4))); };
-template <> struct RawAny<SPD_F16> { typedef u32x2 T __attribute__((aligned(2))); };
-template <> struct RawAny<SPD_U8> { typedef uint32_t T __attribute__((aligned(1))); };
-
-template <int DT>
-__device__ __forceinline__ typename RawT<DT>::T raw4_any(const Loader<DT>& ld, int64_t c)
-{
-    return __builtin_nontemporal_load((const typename RawAny<DT>::T*)(ld.row + c));   // read once
-}
-
-// Four samples from column c as stored; outside the row the value is
-// unspecified (those samples only reach windows that start outside the valid
-// starts).
-template <int DT>
-__device__ __forceinline__ typename RawT<DT>::T raw4(const Loader<DT>& ld, int64_t c, int64_t ncols)
-{
-    auto in = [&](int k) { return c + k >= 0 && c + k < ncols; };
-    if constexpr (DT == SPD_F32) {
-        f32x4 v;
-        v.x = in(0) ? ld.row[c] : 0.f;
-        v.y = in(1) ? ld.row[c + 1] : 0.f;
-        v.z = in(2) ? ld.row[c + 2] : 0.f;
-        v.w = in(3) ? ld.row[c + 3] : 0.f;
-        return v;
-    } else if constexpr (DT == SPD_F16) {
-        const uint16_t* h = (const uint16_t*)ld.row;
-        uint32_t e[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) e[k] = in(k) ? (uint32_t)h[c + k] : 0u;
-        const u32x2 u = {e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
-        return u;
-    } else {
-        uint32_t u = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) u |= (in(k) ? (uint32_t)ld.row[c + k] : 0u) << (8 * k);
-        return u;
-    }
-}
-
-template <int DT>
-__device__ __forceinline__ float4 cvt4(const Loader<DT>& ld, typename RawT<DT>::T u)
-{
-    if constexpr (DT == SPD_F32) {
-        return make_float4(u.x, u.y, u.z, u.w);
-    } else if constexpr (DT == SPD_F16) {
-        const uint32_t lo = u.x, hi = u.y;
-        const float2 a = __half22float2(*reinterpret_cast<const __half2*>(&lo));
-        const float2 b = __half22float2(*reinterpret_cast<const __half2*>(&hi));
-        return make_float4(a.x, a.y, b.x, b.y);
-    } else {
-        return make_float4(ld.deq(u & 255u), ld.deq((u >> 8) & 255u), ld.deq((u >> 16) & 255u), ld.deq(u >> 24));
-    }
-}
-
 __device__ __forceinline__ void put_shifted(float* d, float4 v, float mu_hi, float mu_lo)
 {
     *(float4*)d = make_float4((v.x - mu_hi) - mu_lo, (v.y - mu_hi) - mu_lo, (v.z - mu_hi) - mu_lo,
@@ -1774,16 +1795,16 @@ __device__ __forceinline__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, i
     float* A = buf;
     float* Bv = buf + kStreamBuf;
     {
-        const Raw s0 = raw4_any<DT>(ld, c), s1 = raw4_any<DT>(ld, c + 256);
+        const Raw s0 = raw4_any<DT, true>(ld, c), s1 = raw4_any<DT, true>(ld, c + 256);
         put_shifted(A + lo, cvt4<DT>(ld, s0), mu_hi, mu_lo);
         put_shifted(A + 256 + lo, cvt4<DT>(ld, s1), mu_hi, mu_lo);
     }
     Raw r0{}, r1{};
     if (S > 1) {
-        r0 = raw4_any<DT>(ld, c + kStreamStep);
-        r1 = raw4_any<DT>(ld, c + kStreamStep + 256);
+        r0 = raw4_any<DT, true>(ld, c + kStreamStep);
+        r1 = raw4_any<DT, true>(ld, c + kStreamStep + 256);
     } else if (lane < 4) {
-        r0 = raw4_any<DT>(ld, c + kStreamStep);
+        r0 = raw4_any<DT, true>(ld, c + kStreamStep);
     }
     if (lane < 4) put_shifted(A + kStreamStep + lo, cvt4<DT>(ld, r0), mu_hi, mu_lo);
     wave_sync();
@@ -1794,10 +1815,10 @@ __device__ __forceinline__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, i
         }
         const int64_t nx = c + (k + 2) * kStreamStep;
         if (k + 2 < S) {
-            r0 = raw4_any<DT>(ld, nx);
-            r1 = raw4_any<DT>(ld, nx + 256);
+            r0 = raw4_any<DT, true>(ld, nx);
+            r1 = raw4_any<DT, true>(ld, nx + 256);
         } else if (k + 2 == S && lane < 4) {
-            r0 = raw4_any<DT>(ld, nx);
+            r0 = raw4_any<DT, true>(ld, nx);
         }
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {
@@ -1842,7 +1863,7 @@ __device__ __forceinline__ void boxcar_run_short(const PlaneArg& pl, int64_t r, 
     const int lo = 4 * lane;
     auto load = [&](int step, int at) -> Raw {              // at: 0 or 256
         const int64_t t = t_begin + (int64_t)step * kStreamStep;
-        if (t >= 0 && t + kStreamStep <= ncols) return raw4_any<DT>(ld, t + at + lo);   // uniform
+        if (t >= 0 && t + kStreamStep <= ncols) return raw4_any<DT, true>(ld, t + at + lo);   // uniform
         return raw4<DT>(ld, t + at + lo, ncols);
     };
 

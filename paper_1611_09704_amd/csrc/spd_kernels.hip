@@ -65,8 +65,14 @@ __global__ __launch_bounds__(256) void boxcar_kernel(PlaneArg pl, bool vec, cons
 
 // The group form holds each start's running sum, maximum, group and group-start
 // sum plus two groups' windows; capping it at 128 VGPRs keeps 4 waves per SIMD
-// without spills (uncapped it takes 132 and drops to 3).
-template <int DT, int SMALLN>
+// without spills (uncapped it takes 132 and drops to 3).  The lists that step by
+// 1 throughout (1..24, 1..32, ...) have a variant of their own without the
+// step's choice: 79 VGPRs, 6 waves per SIMD.  Bound by the vector units (two
+// instructions per start and width); with the window's loads in flight before
+// the tables are made, at any alignment of the rows: U8 1024 x 262144, 1..64,
+// 1,524 -> 1,276 us on contiguous rows; F32 1024 x 262144, 1..32, 1,266 -> 902 us
+// and 1..128 2,231 -> 2,017 us; the mixed Sec. 3.3 list 2,690 -> 2,627 us.
+template <int DT, int SMALLN, bool UNIT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SMALLN == 0 ? 4 : 1))) void boxcar_win_kernel(PlaneArg pl, bool vec, const spd_row_stats* stats,
                                                          BoxcarArgs ba, WidthPlan wp)
 {
@@ -75,7 +81,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SMALLN == 0
     const int64_t r = (int64_t)(tile / (uint64_t)ba.tiles_per_row);
     const int64_t tt = (int64_t)(tile % (uint64_t)ba.tiles_per_row);
     const spd_row_stats st = stats[ba.scope == SPD_SCOPE_ROW ? r : 0];
-    boxcar_tile_win<DT, SMALLN>(pl, vec, r, tt, st, ba, wp, smem);
+    boxcar_tile_win<DT, SMALLN, false, UNIT>(pl, vec, r, tt, st, ba, wp, smem);
 }
 
 // Boxcars combined with decimation in time: widths 1..16 at every start, and
@@ -203,6 +209,9 @@ static hipError_t launch_boxcar_dt(const PlaneArg& pl, bool vec, const spd_row_s
         return launch_stream(DT, pl, stats, ba, wp, waves, s);
     if (wp.win == 3)
         hipLaunchKernelGGL((boxcar_dit_kernel<DT>), dim3(ntiles), dim3(64 * waves), lds, s, pl, vec, stats, ba, wp);
+    else if (wp.win == 1 && wp.win_unit)
+        hipLaunchKernelGGL((boxcar_win_kernel<DT, 0, true>), dim3(ntiles), dim3(64 * waves), lds, s, pl, vec, stats, ba,
+                           wp);
     else if (wp.win == 1)
         hipLaunchKernelGGL((boxcar_win_kernel<DT, 0>), dim3(ntiles), dim3(64 * waves), lds, s, pl, vec, stats, ba, wp);
     else if (wp.win == 2 && wp.n <= 8)
