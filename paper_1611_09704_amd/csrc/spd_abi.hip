@@ -544,14 +544,14 @@ spd_status boxcar_snr_dit(const spd_plane* x, const spd_params* p, int32_t level
     if ((st = plan_boxcar(x, p, stats, snr_out, widx_out, out_stride, t_offset, cand, cand_capacity, cand_count,
                           bp)))
         return st;
-    // the decimated layout: x' in padded rows of 9, then one region per level
+    // the decimated layout: x' in padded rows of 9, then level 1; the further levels take the two regions in turn
     WidthPlan& wp = bp.wp;
     BoxcarArgs& ba = bp.ba;
     const int X = kWinX;
     const int nlog = 64 * X + wp.nmax + 8;
     const int npw = (nlog + 7) / 8 * 9;
-    int wave_floats = npw;
-    for (int lv = 1; lv <= levels; ++lv) wave_floats += dit_level_floats(levels, lv);
+    static_assert(dit_level_floats(kDitMaxLevels, 3) <= dit_level_floats(kDitMaxLevels, 1), "level 3 in level 1's region");
+    int wave_floats = npw + (levels ? dit_level_floats(levels, 1) : 0);
     wave_floats = (std::max(wave_floats, 64 * X + 16 * X) + 3) & ~3;
     const size_t tables = (size_t)kWinTableFloats * 4;
     if (tables + (size_t)wave_floats * 4 > 65536) return fail(SPD_E_UNSUPPORTED, "decimated window does not fit in LDS");

@@ -1246,7 +1246,8 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
     float* coef = smem;                                             // 1/sigma_w; NaN past n
     uint32_t* tgb = (uint32_t*)(coef + kMaxWidthsPadded);           // per group: padded offset of its reads
     uint32_t* tgs = tgb + kMaxGroups;                               // per group: step d
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, nwaves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float* arrs = smem + kWinTableFloats + (size_t)wave * ba.wave_floats;
     const int64_t tw = tt * (int64_t)(nwaves * 64 * X) + (int64_t)wave * 64 * X;
     const int rows9 = ba.npw / 9;                                   // rows of 8 logical floats per array
@@ -1420,9 +1421,9 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
             auto level = [&](auto lv_c) {
                 constexpr int LV = decltype(lv_c)::value;
                 constexpr int S = LV < 4 ? (8 >> LV) : 1;              // decimated starts per lane
-                float* dst = lev;
-                for (int l2 = 1; l2 < LV; ++l2) dst += dit_level_floats(levels, l2);
-                const float* src = LV == 1 ? arrs : dst - dit_level_floats(levels, LV - 1);
+                // two regions in turn: level 1 after x', level 2 over x', ...
+                float* dst = LV & 1 ? lev : arrs;
+                const float* src = LV & 1 ? arrs : lev;
                 const int n = dit_level_len(levels, LV);
                 // k = lane + 64 i: every padded index is the lane's plus a multiple of
                 // i known at compile time (the pads repeat every 8, 4 or 2 elements),
