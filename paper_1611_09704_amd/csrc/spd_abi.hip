@@ -241,9 +241,11 @@ spd_status check_msd_workspace(const spd_plane* x, const MsdLayout& m, const voi
 }
 
 // Block partials (Sec. 2.1) then the FP64 merge and sigma_N coefficients
-// (Sec. 2.1-2.2) of every unit of x, on s.  Arguments already validated.
+// (Sec. 2.1-2.2) of every unit of x, on s.  Arguments already validated.  `zero`
+// (may be NULL): the candidate count of the boxcars that follow on s, reset here
+// so that it takes no launch of its own.
 spd_status enqueue_msd(const spd_plane* x, const spd_params* p, int64_t new_col_begin, bool accumulate,
-                       spd_msd_state* state, spd_row_stats* stats, double* part, const MsdLayout& m, hipStream_t s)
+                       spd_msd_state* state, spd_row_stats* stats, double* part, const MsdLayout& m, int64_t* zero, hipStream_t s)
 {
     const int nmax = p->widths[p->n_widths - 1];
     const int64_t nout = x->n_cols - nmax + 1;
@@ -255,7 +257,7 @@ spd_status enqueue_msd(const spd_plane* x, const spd_params* p, int64_t new_col_
     const int64_t units = plane ? 1 : x->n_rows;
     const int64_t per_unit = plane ? x->n_rows * m.nblk : m.nblk;
     e = launch_finalize(part, units, per_unit, need_y, accumulate, state, stats, nmax, p->sigma_mode,
-                        (double)p->auto_kappa, s);
+                        (double)p->auto_kappa, zero, s);
     return device_status(e, "msd finalize launch");
 }
 
@@ -425,7 +427,7 @@ spd_status msd_compute(const spd_plane* x, const spd_params* p, int64_t new_col_
     const MsdLayout m = msd_layout(x);
     if ((st = check_msd_workspace(x, m, workspace, workspace_bytes))) return st;
     return enqueue_msd(x, p, new_col_begin, accumulate != 0, state, stats, (double*)workspace, m,
-                       (hipStream_t)stream);
+                       nullptr, (hipStream_t)stream);
 }
 
 spd_status boxcar_snr(const spd_plane* x, const spd_params* p, const spd_row_stats* stats, float* snr_out,
@@ -472,11 +474,11 @@ spd_status spd_detect(const spd_plane* x, const spd_params* p, spd_row_stats* st
     if (pipelined && (st = detect_events(&ev))) return st;
 
     hipError_t e;
-    if (cand && (e = launch_zero_count(cand_count, s)) != hipSuccess) return device_status(e, "count reset launch");
     if (!pipelined) {
-        if ((st = enqueue_msd(x, p, 0, false, nullptr, stats, part, m, s))) return st;
+        if ((st = enqueue_msd(x, p, 0, false, nullptr, stats, part, m, cand ? cand_count : nullptr, s))) return st;
         return enqueue_boxcar(x, stats, bp, 0, x->n_rows, s);
     }
+    if (cand && (e = launch_zero_count(cand_count, s)) != hipSuccess) return device_status(e, "count reset launch");
     // fork: the statistics stream starts after everything already on `stream`
     if ((e = hipEventRecord(ev[0], s)) != hipSuccess) return device_status(e, "event record");
     if ((e = hipStreamWaitEvent(a, ev[0], 0)) != hipSuccess) return device_status(e, "stream wait");
@@ -486,7 +488,7 @@ spd_status spd_detect(const spd_plane* x, const spd_params* p, spd_row_stats* st
         const int64_t rc = std::min<int64_t>(per, x->n_rows - r0);
         const spd_plane sub = row_slice(x, r0, rc);
         // the chunk's partials use the whole plane's block layout, so they fit the workspace
-        if ((st = enqueue_msd(&sub, p, 0, false, nullptr, stats + r0, part, m, a))) return st;
+        if ((st = enqueue_msd(&sub, p, 0, false, nullptr, stats + r0, part, m, nullptr, a))) return st;
         if ((e = hipEventRecord(ev[k + 1], a)) != hipSuccess) return device_status(e, "event record");
         if ((e = hipStreamWaitEvent(s, ev[k + 1], 0)) != hipSuccess) return device_status(e, "stream wait");
         if ((st = enqueue_boxcar(&sub, stats + r0, bp, r0, rc, s))) return st;
@@ -517,9 +519,7 @@ spd_status spd_detect_static(const spd_plane* x, const spd_params* p, spd_row_st
     double* part = nullptr;
     if ((st = static_scratch(&part))) return st;
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e;
-    if (cand && (e = launch_zero_count(cand_count, s)) != hipSuccess) return device_status(e, "count reset launch");
-    if ((st = enqueue_msd(x, p, 0, false, nullptr, stats, part, m, s))) return st;
+    if ((st = enqueue_msd(x, p, 0, false, nullptr, stats, part, m, cand ? cand_count : nullptr, s))) return st;
     return enqueue_boxcar(x, stats, bp, 0, x->n_rows, s);
 }
 

@@ -33,7 +33,7 @@ struct BoxcarPlan {
 
 spd_status check_msd_workspace(const spd_plane* x, const MsdLayout& m, const void* workspace, size_t bytes);
 spd_status enqueue_msd(const spd_plane* x, const spd_params* p, int64_t new_col_begin, bool accumulate,
-                       spd_msd_state* state, spd_row_stats* stats, double* part, const MsdLayout& m, hipStream_t s);
+                       spd_msd_state* state, spd_row_stats* stats, double* part, const MsdLayout& m, int64_t* zero, hipStream_t s);
 spd_status plan_boxcar(const spd_plane* x, const spd_params* p, const spd_row_stats* stats, float* snr_out,
                        uint8_t* widx_out, int64_t out_stride, int64_t t_offset, spd_candidate* cand,
                        int64_t cand_capacity, int64_t* cand_count, BoxcarPlan& bp);

@@ -2,16 +2,17 @@
 // persistent launch per step (Sec. 2.1-2.4 applied to every beam).
 //
 // A plan owns the per-beam descriptors, the block partials, the per-row
-// statistics and two work-queue counters.  A run is five launches:
-//   fill (queue counters)  ->  batch_msd_kernel (persistent; items are
-//   (beam, row, column block))  ->  batch_finalize_kernel (one work-group per
-//   row of every beam)  ->  fill (candidate count)  ->  batch_boxcar_kernel
-//   (persistent; items are (beam, row, time tile), fused threshold,
-//   candidates only).
+// statistics and a work-queue counter.  A run is three launches:
+//   batch_msd_kernel (items are (beam, row, column block))
+//   -> batch_finalize_lanes_kernel (a few lanes per row of every beam; a
+//   work-group per row where rows have more than 64 blocks; also clears the
+//   candidate count)
+//   -> the boxcar kernel (items are (beam, row, time tile), fused threshold,
+//   candidates only), one work-group per item or persistent.
 // Persistent work-groups take chunks of consecutive items from an atomic
-// counter until it passes the total, so every wave reaches the exit.  The
-// five launches can be captured once into a hipGraph and replayed; counters
-// are cleared by a fill kernel, never by a memset node.
+// counter, cleared by a fill kernel before the run (never by a memset node),
+// until it passes the total, so every wave reaches the exit.  The launches can
+// be captured once into a hipGraph and replayed.
 //
 // The autotuner times the boxcar kernel on the plan's own data for a few
 // schedules (outputs per lane, waves per work-group, work-groups per CU) and
@@ -37,6 +38,7 @@ namespace spd {
 
 constexpr int kMaxBeams = 256;
 constexpr int64_t kMsdBlockCols = 32768;
+constexpr int kMsdWgsPerCu = 64;              // statistics work-groups per CU before they take several items
 constexpr size_t kBatchLdsReserve = 4096;     // static LDS of the persistent kernels (beam table)
 
 struct BeamDesc {
@@ -59,15 +61,21 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// beam holding item `it` given ascending starts s[0..n); wave-uniform
-__device__ __forceinline__ int find_beam(const int64_t* s, int n, int64_t it)
+// beam holding item `it` given ascending starts s[0..n)
+__device__ __forceinline__ int find_beam_lane(const int64_t* s, int n, int64_t it)
 {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (s[mid] <= it) lo = mid; else hi = mid - 1;
     }
-    return __builtin_amdgcn_readfirstlane(lo);
+    return lo;
+}
+
+// the same where `it` is wave-uniform
+__device__ __forceinline__ int find_beam(const int64_t* s, int n, int64_t it)
+{
+    return __builtin_amdgcn_readfirstlane(find_beam_lane(s, n, it));
 }
 
 // Next chunk of items for the whole work-group; uniform result.
@@ -80,47 +88,67 @@ __device__ __forceinline__ int64_t grab_items(int64_t* queue, int grab, int64_t*
     return g0;
 }
 
+// One work-group per item up to kMsdWgsPerCu per CU: bound by HBM, and a queue's
+// atomic and barriers per two items held it back (128 small beams 100 -> 75 us).
 template <int DT, bool WITH_Y>
 __global__ __launch_bounds__(256) void batch_msd_kernel(const BeamDesc* beams, int n_beams, int64_t total,
-                                                        int64_t* queue, int grab, int32_t nmax, double* part)
+                                                        int32_t nmax, double* part)
 {
     __shared__ MsdScratch sh;
     __shared__ int64_t starts[kMaxBeams];
-    __shared__ int64_t slot;
     for (int b = threadIdx.x; b < n_beams; b += blockDim.x) starts[b] = beams[b].msd_start;
     __syncthreads();
-    for (;;) {
-        const int64_t g0 = grab_items(queue, grab, &slot);
-        if (g0 >= total) break;
-        const int64_t g1 = min(g0 + (int64_t)grab, total);
-        for (int64_t it = g0; it < g1; ++it) {
-            const int b = find_beam(starts, n_beams, it);
-            const BeamDesc d = beams[b];
-            const int64_t local = it - d.msd_start;
-            const int64_t r = local / d.nblk, blk = local % d.nblk;
-            double* out6 = part + it * 6;
-            if (WITH_Y)
-                msd_block_xy<DT>(d.pl, d.vec != 0, r, blk, 0, kMsdBlockCols, nmax, d.nout, out6, sh);
-            else
-                msd_block_x<DT>(d.pl, d.vec != 0, r, blk, 0, kMsdBlockCols, out6, sh);
-        }
+    for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
+        const int b = find_beam(starts, n_beams, it);
+        const BeamDesc d = beams[b];
+        const int64_t local = it - d.msd_start;
+        const int64_t r = local / d.nblk, blk = local % d.nblk;
+        double* out6 = part + it * 6;
+        if (WITH_Y)
+            msd_block_xy<DT>(d.pl, d.vec != 0, r, blk, 0, kMsdBlockCols, nmax, d.nout, out6, sh);
+        else
+            msd_block_x<DT>(d.pl, d.vec != 0, r, blk, 0, kMsdBlockCols, out6, sh);
+        __syncthreads();                               // the scratch is free for the next item
     }
 }
 
+// `zero` (may be NULL): the candidate count of the boxcars that follow.
 __global__ __launch_bounds__(256) void batch_finalize_kernel(const BeamDesc* beams, int n_beams,
                                                              const double* part, spd_row_stats* stats,
                                                              int32_t need_y, int32_t nmax, int32_t mode,
-                                                             double kappa)
+                                                             double kappa, int64_t* zero)
 {
     __shared__ FinalizeScratch sh;
     __shared__ int64_t starts[kMaxBeams];
     for (int b = threadIdx.x; b < n_beams; b += blockDim.x) starts[b] = beams[b].unit_start;
     __syncthreads();
     const int64_t u = blockIdx.x;
+    if (zero && u == 0 && threadIdx.x == 0) *zero = 0;
     const int b = find_beam(starts, n_beams, u);
     const BeamDesc d = beams[b];
     const int64_t first_item = d.msd_start + (u - d.unit_start) * d.nblk;
     finalize_unit(part + first_item * 6, d.nblk, need_y != 0, false, nullptr, stats + u, nmax, mode, kappa, sh);
+}
+
+// The same where every beam's rows have at most `lanes` blocks: 256 / lanes rows
+// per work-group (on 128 small beams a work-group per row took 23 us, most of it
+// work-groups starting; this takes 4.8).
+__global__ __launch_bounds__(256) void batch_finalize_lanes_kernel(const BeamDesc* beams, int n_beams, int64_t units,
+                                                                   int32_t lanes, const double* part,
+                                                                   spd_row_stats* stats, int32_t need_y, int32_t nmax,
+                                                                   int32_t mode, double kappa, int64_t* zero)
+{
+    __shared__ int64_t starts[kMaxBeams];
+    for (int b = threadIdx.x; b < n_beams; b += blockDim.x) starts[b] = beams[b].unit_start;
+    __syncthreads();
+    if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
+    const int64_t u = (int64_t)blockIdx.x * (256 / lanes) + threadIdx.x / lanes;
+    const bool on = u < units;
+    const int b = on ? find_beam_lane(starts, n_beams, u) : 0;
+    const int64_t nblk = beams[b].nblk;
+    const int64_t first_item = on ? beams[b].msd_start + (u - beams[b].unit_start) * nblk : 0;
+    finalize_unit_lanes(part + first_item * 6, (int)nblk, lanes, on, need_y != 0, false, nullptr, stats + u, nmax, mode,
+                        kappa);
 }
 
 template <int DT, int X, bool UNIT>
@@ -237,7 +265,7 @@ struct spd_batch_plan {
     spd::BeamDesc* d_beams[spd::kLayouts] = {nullptr, nullptr, nullptr};   // tile numbering differs per slot
     double* d_part = nullptr;
     spd_row_stats* d_stats = nullptr;
-    int64_t* d_counters = nullptr;          // [0] msd queue, [1] boxcar queue, [2] scratch count
+    int64_t* d_counters = nullptr;          // [0] boxcar queue, [1] scratch count
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t capture_stream = nullptr;
@@ -253,17 +281,45 @@ static int xi(int X) { return X == 4 ? 0 : 1; }
 static int slot(const Schedule& sc) { return sc.win ? 2 : xi(sc.X); }
 
 template <int DT>
-static hipError_t enqueue_msd(spd_batch_plan* P, hipStream_t s)
+static hipError_t launch_batch_msd(spd_batch_plan* P, hipStream_t s)
 {
     const bool need_y = P->params.sigma_mode != SPD_SIGMA_SQRTN;
     const int nmax = P->widths.back();
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(P->msd_items, (int64_t)P->cus * 8));
+    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(P->msd_items, (int64_t)P->cus * kMsdWgsPerCu));
     if (need_y)
         hipLaunchKernelGGL((batch_msd_kernel<DT, true>), dim3(grid), dim3(256), 0, s, P->d_beams[1], P->n_beams,
-                           P->msd_items, P->d_counters, 2, nmax, P->d_part);
+                           P->msd_items, nmax, P->d_part);
     else
         hipLaunchKernelGGL((batch_msd_kernel<DT, false>), dim3(grid), dim3(256), 0, s, P->d_beams[1], P->n_beams,
-                           P->msd_items, P->d_counters, 2, nmax, P->d_part);
+                           P->msd_items, nmax, P->d_part);
+    return hipGetLastError();
+}
+
+// Statistics of every row of every beam, and the candidate count reset.
+static hipError_t enqueue_stats(spd_batch_plan* P, int64_t* zero, hipStream_t s)
+{
+    hipError_t e;
+    switch (P->dtype) {
+    case SPD_F32: e = launch_batch_msd<SPD_F32>(P, s); break;
+    case SPD_F16: e = launch_batch_msd<SPD_F16>(P, s); break;
+    default: e = launch_batch_msd<SPD_U8>(P, s); break;
+    }
+    if (e != hipSuccess) return e;
+    const int32_t need_y = P->params.sigma_mode != SPD_SIGMA_SQRTN, nmax = P->widths.back(), mode = P->params.sigma_mode;
+    const double kappa = (double)P->params.auto_kappa;
+    int64_t nblk = 1;
+    for (const auto& d : P->host_beams) nblk = std::max(nblk, d.nblk);
+    if (nblk <= kFinalizeLanes) {
+        int lanes = 1;
+        while (lanes < nblk) lanes <<= 1;
+        const int64_t per_wg = 256 / lanes;
+        hipLaunchKernelGGL(batch_finalize_lanes_kernel, dim3((unsigned)((P->units + per_wg - 1) / per_wg)), dim3(256), 0, s,
+                           P->d_beams[1], P->n_beams, P->units, lanes, P->d_part, P->d_stats, need_y, nmax, mode, kappa,
+                           zero);
+    } else {
+        hipLaunchKernelGGL(batch_finalize_kernel, dim3((unsigned)P->units), dim3(256), 0, s, P->d_beams[1], P->n_beams,
+                           P->d_part, P->d_stats, need_y, nmax, mode, kappa, zero);
+    }
     return hipGetLastError();
 }
 
@@ -287,10 +343,10 @@ static hipError_t enqueue_boxcar_x(spd_batch_plan* P, const Schedule& sc, const 
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(total, (int64_t)P->cus * sc.wgs_per_cu));
     if (P->wp[k].unit_counts)
         hipLaunchKernelGGL((batch_boxcar_kernel<DT, X, true>), dim3(grid), dim3(64 * sc.waves), lds, s,
-                           P->d_beams[k], P->n_beams, total, P->d_counters + 1, sc.grab, P->d_stats, ba, P->wp[k]);
+                           P->d_beams[k], P->n_beams, total, P->d_counters, sc.grab, P->d_stats, ba, P->wp[k]);
     else
         hipLaunchKernelGGL((batch_boxcar_kernel<DT, X, false>), dim3(grid), dim3(64 * sc.waves), lds, s,
-                           P->d_beams[k], P->n_beams, total, P->d_counters + 1, sc.grab, P->d_stats, ba, P->wp[k]);
+                           P->d_beams[k], P->n_beams, total, P->d_counters, sc.grab, P->d_stats, ba, P->wp[k]);
     return hipGetLastError();
 }
 
@@ -345,19 +401,10 @@ static hipError_t enqueue_boxcar_dt(spd_batch_plan* P, const Schedule& sc, spd_c
 
 static hipError_t enqueue_run(spd_batch_plan* P, spd_candidate* cand, int64_t cap, int64_t* count, hipStream_t s)
 {
-    hipError_t e = launch_fill_i64(P->d_counters, 2, 0, s);
-    if (e != hipSuccess) return e;
-    switch (P->dtype) {
-    case SPD_F32: e = enqueue_msd<SPD_F32>(P, s); break;
-    case SPD_F16: e = enqueue_msd<SPD_F16>(P, s); break;
-    default: e = enqueue_msd<SPD_U8>(P, s); break;
-    }
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(batch_finalize_kernel, dim3((unsigned)P->units), dim3(256), 0, s, P->d_beams[1], P->n_beams,
-                       P->d_part, P->d_stats, (int32_t)(P->params.sigma_mode != SPD_SIGMA_SQRTN),
-                       (int32_t)P->widths.back(), (int32_t)P->params.sigma_mode, (double)P->params.auto_kappa);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = launch_fill_i64(count, 1, 0, s)) != hipSuccess) return e;
+    hipError_t e;
+    // the persistent schedules' queue; the grid launches have none
+    if (P->sched.wgs_per_cu != 0 && !P->sched.win && (e = launch_fill_i64(P->d_counters, 1, 0, s)) != hipSuccess) return e;
+    if ((e = enqueue_stats(P, count, s)) != hipSuccess) return e;
     return enqueue_boxcar_dt(P, P->sched, cand, cap, count, -1, s);
 }
 
@@ -485,17 +532,8 @@ static spd_status tune(spd_batch_plan* P, hipStream_t s)
         P->tuned = 2;
         return SPD_OK;
     }
-    hipError_t e = launch_fill_i64(P->d_counters, 4, 0, s);
-    if (e != hipSuccess) return device_status(e, "tune reset");
-    switch (P->dtype) {
-    case SPD_F32: e = enqueue_msd<SPD_F32>(P, s); break;
-    case SPD_F16: e = enqueue_msd<SPD_F16>(P, s); break;
-    default: e = enqueue_msd<SPD_U8>(P, s); break;
-    }
-    if (e != hipSuccess) return device_status(e, "tune msd");
-    hipLaunchKernelGGL(batch_finalize_kernel, dim3((unsigned)P->units), dim3(256), 0, s, P->d_beams[1], P->n_beams,
-                       P->d_part, P->d_stats, (int32_t)(P->params.sigma_mode != SPD_SIGMA_SQRTN),
-                       (int32_t)P->widths.back(), (int32_t)P->params.sigma_mode, (double)P->params.auto_kappa);
+    hipError_t e = enqueue_stats(P, nullptr, s);
+    if (e != hipSuccess) return device_status(e, "tune statistics");
     hipEvent_t e0, e1;
     hipEventCreate(&e0);
     hipEventCreate(&e1);
@@ -523,9 +561,9 @@ static spd_status tune(spd_batch_plan* P, hipStream_t s)
                 const int64_t limit = std::min<int64_t>(P->tiles[k], (int64_t)P->cus * 6 * 8 * 6);
                 float ms = 0.f;
                 for (int rep = 0; rep < 2; ++rep) {
-                    launch_fill_i64(P->d_counters + 1, 2, 0, s);
+                    launch_fill_i64(P->d_counters, 2, 0, s);
                     hipEventRecord(e0, s);
-                    e = enqueue_boxcar_dt(P, sc, nullptr, 0, P->d_counters + 2, limit, s);
+                    e = enqueue_boxcar_dt(P, sc, nullptr, 0, P->d_counters + 1, limit, s);
                     hipEventRecord(e1, s);
                     if (e != hipSuccess) break;
                     hipEventSynchronize(e1);

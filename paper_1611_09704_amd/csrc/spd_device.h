@@ -836,11 +836,46 @@ struct FinalizeScratch {
     Msd64 x[256], y[256];
 };
 
-// One unit's statistics from its `per_unit` block partials p[per_unit][6]:
-// thread j merges a contiguous run in order, then a fixed neighbour tree
-// merges the runs (deterministic).  Thread 0 merges the result into the
-// running state (when given), then writes mean, sigma, sigma_Nmax and the
-// coefficient of Eq. (sd03) for the sigma mode.
+// Merges the unit's totals X, Y into the running state (when given), then
+// writes mean, sigma, sigma_Nmax and the coefficient of Eq. (sd03) for the
+// sigma mode.
+__device__ __forceinline__ void write_stats(Msd64 X, Msd64 Y, bool need_y, bool accumulate, spd_msd_state* state,
+                                            spd_row_stats* stats, int32_t nmax, int32_t mode, double kappa)
+{
+    if (state) {
+        const spd_msd_state st = *state;
+        if (accumulate) {
+            X = merge64(Msd64{st.n, st.T, st.S}, X);
+            Y = merge64(Msd64{st.n_y, st.T_y, st.S_y}, Y);
+        }
+        *state = spd_msd_state{X.n, X.T, X.S, Y.n, Y.T, Y.S};
+    }
+    spd_row_stats o;
+    o.mean = X.n > 0.0 ? X.T / X.n : 0.0;
+    o.sigma = X.n > 0.0 ? sqrt(X.S / X.n) : 0.0;
+    o.sigma_nmax = (need_y && Y.n > 0.0) ? sqrt(Y.S / Y.n) : 0.0;
+    o.lin_coef = 0.0;
+    o.flags = 0;
+    o.reserved0 = 0;
+    if (!(o.sigma > 0.0)) {
+        o.flags |= SPD_FLAG_ZERO_VAR;
+    } else if (nmax > 1 && mode != SPD_SIGMA_SQRTN) {
+        const double base = sqrt((double)nmax) * o.sigma;
+        const double anchored = (o.sigma_nmax - base) / (double)(nmax - 1);
+        if (mode == SPD_SIGMA_LINEAR) {
+            o.lin_coef = anchored; o.flags |= SPD_FLAG_LINEAR;
+        } else if (mode == SPD_SIGMA_LINEAR_LITERAL) {
+            o.lin_coef = o.sigma_nmax / (double)(nmax - 1); o.flags |= SPD_FLAG_LINEAR;
+        } else if (mode == SPD_SIGMA_AUTO && o.sigma_nmax / base > 1.0 + kappa) {
+            o.lin_coef = anchored; o.flags |= SPD_FLAG_LINEAR;
+        }
+    }
+    *stats = o;
+}
+
+// One unit's statistics from its `per_unit` block partials p[per_unit][6], by a
+// work-group: thread j merges a contiguous run in order, then a fixed neighbour
+// tree merges the runs (deterministic).
 __device__ void finalize_unit(const double* p, int64_t per_unit, bool need_y, bool accumulate,
                               spd_msd_state* state, spd_row_stats* stats, int32_t nmax, int32_t mode,
                               double kappa, FinalizeScratch& sh)
@@ -862,39 +897,36 @@ __device__ void finalize_unit(const double* p, int64_t per_unit, bool need_y, bo
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        Msd64 X = sh.x[0], Y = sh.y[0];
-        if (state) {
-            const spd_msd_state st = *state;
-            if (accumulate) {
-                X = merge64(Msd64{st.n, st.T, st.S}, X);
-                Y = merge64(Msd64{st.n_y, st.T_y, st.S_y}, Y);
-            }
-            *state = spd_msd_state{X.n, X.T, X.S, Y.n, Y.T, Y.S};
-        }
-        spd_row_stats o;
-        o.mean = X.n > 0.0 ? X.T / X.n : 0.0;
-        o.sigma = X.n > 0.0 ? sqrt(X.S / X.n) : 0.0;
-        o.sigma_nmax = (need_y && Y.n > 0.0) ? sqrt(Y.S / Y.n) : 0.0;
-        o.lin_coef = 0.0;
-        o.flags = 0;
-        o.reserved0 = 0;
-        if (!(o.sigma > 0.0)) {
-            o.flags |= SPD_FLAG_ZERO_VAR;
-        } else if (nmax > 1 && mode != SPD_SIGMA_SQRTN) {
-            const double base = sqrt((double)nmax) * o.sigma;
-            const double anchored = (o.sigma_nmax - base) / (double)(nmax - 1);
-            if (mode == SPD_SIGMA_LINEAR) {
-                o.lin_coef = anchored; o.flags |= SPD_FLAG_LINEAR;
-            } else if (mode == SPD_SIGMA_LINEAR_LITERAL) {
-                o.lin_coef = o.sigma_nmax / (double)(nmax - 1); o.flags |= SPD_FLAG_LINEAR;
-            } else if (mode == SPD_SIGMA_AUTO && o.sigma_nmax / base > 1.0 + kappa) {
-                o.lin_coef = anchored; o.flags |= SPD_FLAG_LINEAR;
-            }
-        }
-        *stats = o;
-    }
+    if (tid == 0) write_stats(sh.x[0], sh.y[0], need_y, accumulate, state, stats, nmax, mode, kappa);
 }
+
+// The same for a unit of at most `lanes` partials (a power of two <= 64) by that
+// many neighbouring lanes of a wave: one partial per lane, and the first levels
+// of the same neighbour tree (the others would merge empty runs, which changes
+// nothing).  `on` is false in the lanes of no unit.
+__device__ __forceinline__ void finalize_unit_lanes(const double* p, int per_unit, int lanes, bool on, bool need_y,
+                                                    bool accumulate, spd_msd_state* state, spd_row_stats* stats,
+                                                    int32_t nmax, int32_t mode, double kappa)
+{
+    const int lane = threadIdx.x & 63, i = lane & (lanes - 1);
+    Msd64 x{0, 0, 0}, y{0, 0, 0};
+    if (on && i < per_unit) {
+        x = Msd64{p[i * 6 + 0], p[i * 6 + 1], p[i * 6 + 2]};
+        if (need_y) y = Msd64{p[i * 6 + 3], p[i * 6 + 4], p[i * 6 + 5]};
+    }
+    for (int h = 1; h < lanes; h <<= 1) {
+        const Msd64 ox{__shfl_down(x.n, h), __shfl_down(x.T, h), __shfl_down(x.S, h)};
+        const Msd64 oy{__shfl_down(y.n, h), __shfl_down(y.T, h), __shfl_down(y.S, h)};
+        if ((i & (2 * h - 1)) == 0) {
+            x = merge64(x, ox);
+            y = merge64(y, oy);
+        }
+    }
+    if (on && i == 0) write_stats(x, y, need_y, accumulate, state, stats, nmax, mode, kappa);
+}
+
+// Units of up to this many partials take finalize_unit_lanes.
+constexpr int kFinalizeLanes = 64;
 
 // ---------------------------------------------------------------------------
 // Sec. 2.3, Algorithm 1: boxcars, SNR, highest SNR and first width; Sec. 2.4

@@ -266,7 +266,6 @@ static spd_status launch_chunk(spd_server* S, ServeReq& r)
         if ((st = plan_boxcar(&x, &S->params, pb.stats, nullptr, nullptr, 0, chunk_t_offset(S, r.seq, r.fresh), pb.d_cand,
                               S->cfg.cand_capacity, pb.d_count, bp)))
             return st;
-        if ((e = launch_zero_count(pb.d_count, cs)) != hipSuccess) return device_status(e, "count reset");
         const int64_t per = (R + kServeRowGroups - 1) / kServeRowGroups;
         for (int g = 0; g < kServeRowGroups; ++g) {
             const int64_t r0 = (int64_t)g * per, rows = std::min<int64_t>(per, R - r0);
@@ -282,7 +281,7 @@ static spd_status launch_chunk(spd_server* S, ServeReq& r)
             if (e != hipSuccess) return device_status(e, "chunk re-pitch");
             const spd_plane sub = row_slice(&x, r0, rows);
             if ((st = enqueue_msd(&sub, &S->params, r.fresh ? 0 : H, r.seq != 0, b.state + r0, pb.stats + r0,
-                                  (double*)b.ws, m, cs)))
+                                  (double*)b.ws, m, g == 0 ? pb.d_count : nullptr, cs)))
                 return st;
             if ((st = enqueue_boxcar(&sub, pb.stats + r0, bp, r0, rows, cs))) return st;
         }
