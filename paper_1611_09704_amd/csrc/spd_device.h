@@ -1540,7 +1540,7 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
                 B[i] = b;
             }
         };
-        const int ng = wp.n / kGroup;                               // n is a multiple of 8 in this form
+        const int ng = (wp.n + kGroup - 1) / kGroup;                // a short last group has NaN coefficients
         // runs of groups with one step; two groups per trip let the carried
         // sums and maxima alternate registers instead of being copied
         for (int g = 0; g < ng;) {
