@@ -78,6 +78,15 @@ __device__ __forceinline__ int find_beam(const int64_t* s, int n, int64_t it)
     return __builtin_amdgcn_readfirstlane(find_beam_lane(s, n, it));
 }
 
+// The beam of item `it` from a table of one byte per item (uniform: a scalar
+// load).  The grid launches use it: a work-group with one item spent its start on
+// loading the beams' starts into LDS and searching them (boxcars of 128 beams,
+// 51,200 tiles: 378 -> 357 us).
+__device__ __forceinline__ int beam_at(const uint32_t* beam_of, int64_t it)
+{
+    return (beam_of[it >> 2] >> (8 * (it & 3))) & 255u;
+}
+
 // Next chunk of items for the whole work-group; uniform result.
 __device__ __forceinline__ int64_t grab_items(int64_t* queue, int grab, int64_t* slot)
 {
@@ -91,18 +100,15 @@ __device__ __forceinline__ int64_t grab_items(int64_t* queue, int grab, int64_t*
 // One work-group per item up to kMsdWgsPerCu per CU: bound by HBM, and a queue's
 // atomic and barriers per two items held it back (128 small beams 100 -> 75 us).
 template <int DT, bool WITH_Y>
-__global__ __launch_bounds__(256) void batch_msd_kernel(const BeamDesc* beams, int n_beams, int64_t total,
+__global__ __launch_bounds__(256) void batch_msd_kernel(const BeamDesc* beams, const uint32_t* beam_of, int64_t total,
                                                         int32_t nmax, double* part)
 {
     __shared__ MsdScratch sh;
-    __shared__ int64_t starts[kMaxBeams];
-    for (int b = threadIdx.x; b < n_beams; b += blockDim.x) starts[b] = beams[b].msd_start;
-    __syncthreads();
     for (int64_t it = blockIdx.x; it < total; it += gridDim.x) {
-        const int b = find_beam(starts, n_beams, it);
+        const int b = beam_at(beam_of, it);
         const BeamDesc d = beams[b];
-        const int64_t local = it - d.msd_start;
-        const int64_t r = local / d.nblk, blk = local % d.nblk;
+        const uint32_t local = (uint32_t)(it - d.msd_start), per = (uint32_t)d.nblk;    // items: 31 bits
+        const int64_t r = local / per, blk = local % per;
         double* out6 = part + it * 6;
         if (WITH_Y)
             msd_block_xy<DT>(d.pl, d.vec != 0, r, blk, 0, kMsdBlockCols, nmax, d.nout, out6, sh);
@@ -186,19 +192,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(X == 4 ? 5 
 // All tiles of all beams in one ordinary launch: work-group i takes tile i
 // (XCD-aware numbering), finds its beam and row, and runs the same tile code.
 template <int DT, int X, bool UNIT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UNIT ? 5 : 1))) void batch_boxcar_grid_kernel(const BeamDesc* beams, int n_beams,
-                                                                const spd_row_stats* stats, BoxcarArgs ba,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UNIT ? 5 : 1))) void batch_boxcar_grid_kernel(const BeamDesc* beams,
+                                                                const uint32_t* beam_of, const spd_row_stats* stats, BoxcarArgs ba,
                                                                 WidthPlan wp)
 {
     extern __shared__ float smem[];
-    __shared__ int64_t starts[kMaxBeams];
-    for (int b = threadIdx.x; b < n_beams; b += blockDim.x) starts[b] = beams[b].tile_start;
-    __syncthreads();
     const int64_t it = (int64_t)xcd_remap(blockIdx.x, gridDim.x);
-    const int b = find_beam(starts, n_beams, it);
+    const int b = beam_at(beam_of, it);
     const BeamDesc d = beams[b];
-    const int64_t local = it - d.tile_start;
-    const int64_t r = local / d.tiles_per_row, tt = local % d.tiles_per_row;
+    const uint32_t local = (uint32_t)(it - d.tile_start), per = (uint32_t)d.tiles_per_row;   // a grid's items: 32 bits
+    const int64_t r = local / per, tt = local % per;
     ba.tiles_per_row = d.tiles_per_row;
     ba.nout = d.nout;
     ba.beam = (uint32_t)b;
@@ -211,17 +214,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UNIT ? 5 : 
 // kernel of the same form.
 template <int DT, int SMALLN, bool UNIT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SMALLN == 0 ? 4 : 6))) void batch_boxcar_win_grid_kernel(
-    const BeamDesc* beams, int n_beams, const spd_row_stats* stats, BoxcarArgs ba, WidthPlan wp)
+    const BeamDesc* beams, const uint32_t* beam_of, const spd_row_stats* stats, BoxcarArgs ba, WidthPlan wp)
 {
     extern __shared__ float smem[];
-    __shared__ int64_t starts[kMaxBeams];
-    for (int b = threadIdx.x; b < n_beams; b += blockDim.x) starts[b] = beams[b].tile_start;
-    __syncthreads();
     const int64_t it = (int64_t)xcd_remap(blockIdx.x, gridDim.x);
-    const int b = find_beam(starts, n_beams, it);
+    const int b = beam_at(beam_of, it);
     const BeamDesc d = beams[b];
-    const int64_t local = it - d.tile_start;
-    const int64_t r = local / d.tiles_per_row, tt = local % d.tiles_per_row;
+    const uint32_t local = (uint32_t)(it - d.tile_start), per = (uint32_t)d.tiles_per_row;   // a grid's items: 32 bits
+    const int64_t r = local / per, tt = local % per;
     ba.tiles_per_row = d.tiles_per_row;
     ba.nout = d.nout;
     ba.beam = (uint32_t)b;
@@ -263,6 +263,7 @@ struct spd_batch_plan {
     int64_t msd_items = 0, tiles[spd::kLayouts] = {0, 0, 0}, units = 0;
     std::vector<spd::BeamDesc> host_beams;
     spd::BeamDesc* d_beams[spd::kLayouts] = {nullptr, nullptr, nullptr};   // tile numbering differs per slot
+    uint32_t* d_beam_of[spd::kLayouts + 1] = {nullptr, nullptr, nullptr, nullptr};   // beam of each tile; last: of each MSD item
     double* d_part = nullptr;
     spd_row_stats* d_stats = nullptr;
     int64_t* d_counters = nullptr;          // [0] boxcar queue, [1] scratch count
@@ -287,11 +288,11 @@ static hipError_t launch_batch_msd(spd_batch_plan* P, hipStream_t s)
     const int nmax = P->widths.back();
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(P->msd_items, (int64_t)P->cus * kMsdWgsPerCu));
     if (need_y)
-        hipLaunchKernelGGL((batch_msd_kernel<DT, true>), dim3(grid), dim3(256), 0, s, P->d_beams[1], P->n_beams,
-                           P->msd_items, nmax, P->d_part);
+        hipLaunchKernelGGL((batch_msd_kernel<DT, true>), dim3(grid), dim3(256), 0, s, P->d_beams[1],
+                           P->d_beam_of[kLayouts], P->msd_items, nmax, P->d_part);
     else
-        hipLaunchKernelGGL((batch_msd_kernel<DT, false>), dim3(grid), dim3(256), 0, s, P->d_beams[1], P->n_beams,
-                           P->msd_items, nmax, P->d_part);
+        hipLaunchKernelGGL((batch_msd_kernel<DT, false>), dim3(grid), dim3(256), 0, s, P->d_beams[1],
+                           P->d_beam_of[kLayouts], P->msd_items, nmax, P->d_part);
     return hipGetLastError();
 }
 
@@ -334,10 +335,10 @@ static hipError_t enqueue_boxcar_x(spd_batch_plan* P, const Schedule& sc, const 
         if ((uint64_t)total * 64u * (uint64_t)sc.waves > kMaxGridItems) return hipErrorInvalidConfiguration;
         if (P->wp[k].unit_counts)
             hipLaunchKernelGGL((batch_boxcar_grid_kernel<DT, X, true>), dim3((unsigned)total), dim3(64 * sc.waves),
-                               lds, s, P->d_beams[k], P->n_beams, P->d_stats, ba, P->wp[k]);
+                               lds, s, P->d_beams[k], P->d_beam_of[k], P->d_stats, ba, P->wp[k]);
         else
             hipLaunchKernelGGL((batch_boxcar_grid_kernel<DT, X, false>), dim3((unsigned)total), dim3(64 * sc.waves),
-                               lds, s, P->d_beams[k], P->n_beams, P->d_stats, ba, P->wp[k]);
+                               lds, s, P->d_beams[k], P->d_beam_of[k], P->d_stats, ba, P->wp[k]);
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(total, (int64_t)P->cus * sc.wgs_per_cu));
@@ -360,16 +361,16 @@ static hipError_t enqueue_boxcar_win(spd_batch_plan* P, const Schedule& sc, cons
     if ((uint64_t)total * 64u * (uint64_t)sc.waves > kMaxGridItems) return hipErrorInvalidConfiguration;
     if (wp.win == 1 && wp.win_unit)
         hipLaunchKernelGGL((batch_boxcar_win_grid_kernel<DT, 0, true>), dim3((unsigned)total), dim3(64 * sc.waves), lds,
-                           s, P->d_beams[2], P->n_beams, P->d_stats, ba, wp);
+                           s, P->d_beams[2], P->d_beam_of[2], P->d_stats, ba, wp);
     else if (wp.win == 1)
         hipLaunchKernelGGL((batch_boxcar_win_grid_kernel<DT, 0>), dim3((unsigned)total), dim3(64 * sc.waves), lds, s,
-                           P->d_beams[2], P->n_beams, P->d_stats, ba, wp);
+                           P->d_beams[2], P->d_beam_of[2], P->d_stats, ba, wp);
     else if (wp.n <= 8)
         hipLaunchKernelGGL((batch_boxcar_win_grid_kernel<DT, 8>), dim3((unsigned)total), dim3(64 * sc.waves), lds, s,
-                           P->d_beams[2], P->n_beams, P->d_stats, ba, wp);
+                           P->d_beams[2], P->d_beam_of[2], P->d_stats, ba, wp);
     else
         hipLaunchKernelGGL((batch_boxcar_win_grid_kernel<DT, 16>), dim3((unsigned)total), dim3(64 * sc.waves), lds,
-                           s, P->d_beams[2], P->n_beams, P->d_stats, ba, wp);
+                           s, P->d_beams[2], P->d_beam_of[2], P->d_stats, ba, wp);
     return hipGetLastError();
 }
 
@@ -470,6 +471,21 @@ static void cache_store(const std::string& key, const Schedule& sc)
 
 using namespace spd;
 
+// One byte per item: items [start(b), start(b + 1)) belong to beam b.
+static hipError_t upload_beam_of(int64_t total, const std::vector<BeamDesc>& v, int64_t BeamDesc::* start, uint32_t** out)
+{
+    std::vector<uint32_t> words((size_t)((total + 3) / 4), 0);
+    uint8_t* t = (uint8_t*)words.data();
+    for (size_t b = 0; b < v.size(); ++b) {
+        const int64_t i0 = v[b].*start, i1 = b + 1 < v.size() ? v[b + 1].*start : total;
+        memset(t + i0, (int)b, (size_t)(i1 - i0));
+    }
+    const size_t bytes = std::max<size_t>(words.size(), 1) * 4;
+    hipError_t e = hipMalloc((void**)out, bytes);
+    if (e == hipSuccess && !words.empty()) e = hipMemcpy(*out, words.data(), words.size() * 4, hipMemcpyHostToDevice);
+    return e;
+}
+
 static spd_status build_beams(spd_batch_plan* P, const spd_plane* beams)
 {
     P->host_beams.resize(P->n_beams);
@@ -506,10 +522,16 @@ static spd_status build_beams(spd_batch_plan* P, const spd_plane* beams)
         if (e != hipSuccess) return device_status(e, "hipMalloc(beams)");
         e = hipMemcpy(P->d_beams[k], v.data(), sizeof(BeamDesc) * P->n_beams, hipMemcpyHostToDevice);
         if (e != hipSuccess) return device_status(e, "hipMemcpy(beams)");
+        // the grid launch's; more tiles than one grid holds take the persistent form
+        if ((uint64_t)t * 64u * (uint64_t)P->max_waves[k] <= kMaxGridItems &&
+            (e = upload_beam_of(t, v, &BeamDesc::tile_start, &P->d_beam_of[k])) != hipSuccess)
+            return device_status(e, "tile table");
     }
     for (int k = 0; k < kLayouts; ++k) P->tiles[k] = tiles[k];
     if (P->units > 0x7fffffffLL || P->msd_items > 0x7fffffffLL)
         return fail(SPD_E_UNSUPPORTED, "batch too large");
+    hipError_t e = upload_beam_of(msd, P->host_beams, &BeamDesc::msd_start, &P->d_beam_of[kLayouts]);
+    if (e != hipSuccess) return device_status(e, "item table");
     return SPD_OK;
 }
 
@@ -751,6 +773,8 @@ void spd_batch_plan_destroy(spd_batch_plan* P)
         if (P->d_beams[k]) hipFree(P->d_beams[k]);
     if (P->d_part) hipFree(P->d_part);
     if (P->d_stats) hipFree(P->d_stats);
+    for (uint32_t* t : P->d_beam_of)
+        if (t) hipFree(t);
     if (P->d_counters) hipFree(P->d_counters);
     delete P;
 }

@@ -445,6 +445,30 @@ __device__ __forceinline__ float wave_inclusive_scan(float x)
     return x;
 }
 
+// Places in the candidate list for a wave's candidates, up to 32 per lane: add()
+// once per start index (all lanes), then take() reserves them with one atomic
+// and returns the lane's first.  An atomic per start index with candidates made
+// a wave on a pulse wait for up to 8 (or 16) of them in turn, at the end of a
+// launch with nothing left to run beside it.
+struct CandSlots {
+    uint32_t mine = 0;                                              // the lane's own, by start index
+    int before = 0, total = 0;                                      // in lower lanes; in the wave
+    __device__ __forceinline__ void add(int i, bool pred)
+    {
+        const uint64_t mask = __ballot(pred);
+        mine |= (uint32_t)pred << i;
+        before += __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+        total += __popcll(mask);
+    }
+    __device__ __forceinline__ bool has(int i) const { return (mine >> i) & 1u; }
+    __device__ __forceinline__ unsigned long long take(int64_t* count) const
+    {
+        unsigned long long base = 0;
+        if (total && (threadIdx.x & 63) == 0) base = atomicAdd((unsigned long long*)count, (unsigned long long)total);
+        return __shfl(base, 0) + (unsigned long long)before;
+    }
+};
+
 // Orders LDS writes and reads between lanes of one wave.
 __device__ __forceinline__ void wave_sync()
 {
@@ -1587,37 +1611,30 @@ __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t
     }
 
     // fused threshold (Sec. 2.4): a wave with no SNR at the threshold skips it; otherwise one
-    // ballot per start index and one atomic per wave with candidates
+    // ballot per start index and one atomic for the wave
     const int64_t left = ba.nout - t0;
     const int nvalid = left <= 0 ? 0 : (left >= X ? X : (int)left);
     float mall = sv[0];
 #pragma unroll
     for (int i = 1; i < X; ++i) mall = fmaxf(mall, sv[i]);
     if (ba.cand && __ballot(mall >= ba.threshold)) {
+        CandSlots slots;
+#pragma unroll
+        for (int i = 0; i < X; ++i) slots.add(i, i < nvalid && sv[i] >= ba.threshold);
+        unsigned long long k = slots.take(ba.cand_count);
 #pragma unroll
         for (int i = 0; i < X; ++i) {
-            const int64_t t = t0 + i;
-            const bool pred = i < nvalid && sv[i] >= ba.threshold;
-            const uint64_t mask = __ballot(pred);
-            if (mask) {
-                const int cntw = __popcll(mask);
-                const int before = __popcll(mask & ((1ull << lane) - 1ull));
-                unsigned long long base = 0;
-                if (lane == 0) base = atomicAdd((unsigned long long*)ba.cand_count, (unsigned long long)cntw);
-                base = __shfl(base, 0);
-                if (pred) {
-                    const unsigned long long k = base + (unsigned long long)before;
-                    if (k < (unsigned long long)ba.cand_capacity) {
-                        spd_candidate cd;
-                        cd.row = (int32_t)r + ba.row0;
-                        cd.width = wp.width[iv[i]];
-                        cd.t = t + ba.t_offset;
-                        cd.snr = sv[i];
-                        cd.beam = ba.beam;
-                        ba.cand[k] = cd;
-                    }
-                }
+            if (!slots.has(i)) continue;
+            if (k < (unsigned long long)ba.cand_capacity) {
+                spd_candidate cd;
+                cd.row = (int32_t)r + ba.row0;
+                cd.width = wp.width[iv[i]];
+                cd.t = t0 + i + ba.t_offset;
+                cd.snr = sv[i];
+                cd.beam = ba.beam;
+                ba.cand[k] = cd;
             }
+            ++k;
         }
     }
     // per-start outputs.  In the grouped form (long width lists, bound by the ALU)
@@ -1747,34 +1764,29 @@ __device__ __forceinline__ void short_block(const float* src, const float (&a)[N
 }
 
 // One candidate per (start, lane) with snr >= threshold among the lane's
-// starts t + i, lo <= i < cnt: one ballot per start index, one atomic per
-// wave and start index that has candidates.
+// starts t + i, lo <= i < cnt: one ballot per start index, one atomic for the
+// wave if it has any.
 __device__ __forceinline__ void emit_block_cands(const BoxcarArgs& ba, const WidthPlan& wp, int64_t r, int64_t t,
                                                  int lo, int cnt, const float (&sv)[4], uint32_t packed)
 {
-    const int lane = threadIdx.x & 63;
+    CandSlots slots;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) slots.add(i, i >= lo && i < cnt && sv[i] >= ba.threshold);
+    if (!slots.total) return;
+    unsigned long long k = slots.take(ba.cand_count);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const bool pred = i >= lo && i < cnt && sv[i] >= ba.threshold;
-        const uint64_t mask = __ballot(pred);
-        if (!mask) continue;
-        const int cntw = __popcll(mask);
-        const int before = __popcll(mask & ((1ull << lane) - 1ull));
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd((unsigned long long*)ba.cand_count, (unsigned long long)cntw);
-        base = __shfl(base, 0);
-        if (pred) {
-            const unsigned long long k = base + (unsigned long long)before;
-            if (k < (unsigned long long)ba.cand_capacity) {
-                spd_candidate cd;
-                cd.row = (int32_t)r + ba.row0;
-                cd.width = wp.width[(packed >> (8 * i)) & 255u];
-                cd.t = t + i + ba.t_offset;
-                cd.snr = sv[i];
-                cd.beam = ba.beam;
-                ba.cand[k] = cd;
-            }
+        if (!slots.has(i)) continue;
+        if (k < (unsigned long long)ba.cand_capacity) {
+            spd_candidate cd;
+            cd.row = (int32_t)r + ba.row0;
+            cd.width = wp.width[(packed >> (8 * i)) & 255u];
+            cd.t = t + i + ba.t_offset;
+            cd.snr = sv[i];
+            cd.beam = ba.beam;
+            ba.cand[k] = cd;
         }
+        ++k;
     }
 }
 

@@ -14,7 +14,7 @@
 //   select_kernel                  threshold over stored outputs, Sec. 2.4
 //
 // One work-group per (row, column block) or (row, time tile), numbered so that
-// each XCD gets a contiguous range.  The arithmetic lives in spd_device.h.
+// each XCD gets a contiguous range (a grid's numbers fit in 32 bits).  The arithmetic lives in spd_device.h.
 #include "spd_device.h"
 #include "spd_kernels.h"
 
@@ -25,9 +25,9 @@ __global__ __launch_bounds__(256) void msd_x_kernel(PlaneArg pl, bool vec, int64
                                                     int64_t nblk, double* part)
 {
     __shared__ MsdScratch sh;
-    const uint64_t wg = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t r = (int64_t)(wg / (uint64_t)nblk), b = (int64_t)(wg % (uint64_t)nblk);
-    msd_block_x<DT>(pl, vec, r, b, ncb, bc, part + wg * 6, sh);
+    const uint32_t wg = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t r = wg / (uint32_t)nblk, b = wg % (uint32_t)nblk;
+    msd_block_x<DT>(pl, vec, r, b, ncb, bc, part + (size_t)wg * 6, sh);
 }
 
 template <int DT>
@@ -35,9 +35,9 @@ __global__ __launch_bounds__(256) void msd_xy_kernel(PlaneArg pl, bool vec, int6
                                                      int64_t nblk, int32_t nmax, int64_t nout, double* part)
 {
     __shared__ MsdScratch sh;
-    const uint64_t wg = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t r = (int64_t)(wg / (uint64_t)nblk), b = (int64_t)(wg % (uint64_t)nblk);
-    msd_block_xy<DT>(pl, vec, r, b, ncb, bc, nmax, nout, part + wg * 6, sh);
+    const uint32_t wg = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t r = wg / (uint32_t)nblk, b = wg % (uint32_t)nblk;
+    msd_block_xy<DT>(pl, vec, r, b, ncb, bc, nmax, nout, part + (size_t)wg * 6, sh);
 }
 
 // `zero` (may be NULL): a counter for the launches after this one to add to.
@@ -75,9 +75,8 @@ __global__ __launch_bounds__(256) void boxcar_kernel(PlaneArg pl, bool vec, cons
                                                      BoxcarArgs ba, WidthPlan wp)
 {
     extern __shared__ float smem[];
-    const uint64_t tile = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t r = (int64_t)(tile / (uint64_t)ba.tiles_per_row);
-    const int64_t tt = (int64_t)(tile % (uint64_t)ba.tiles_per_row);
+    const uint32_t tile = (uint32_t)xcd_remap(blockIdx.x, gridDim.x), per = (uint32_t)ba.tiles_per_row;
+    const int64_t r = tile / per, tt = tile % per;
     const spd_row_stats st = stats[ba.scope == SPD_SCOPE_ROW ? r : 0];
     boxcar_tile<DT, X, UNIT, SMALL>(pl, vec, r, tt, st, ba, wp, smem, true);
 }
@@ -96,9 +95,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SMALLN == 0
                                                          BoxcarArgs ba, WidthPlan wp)
 {
     extern __shared__ float smem[];
-    const uint64_t tile = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t r = (int64_t)(tile / (uint64_t)ba.tiles_per_row);
-    const int64_t tt = (int64_t)(tile % (uint64_t)ba.tiles_per_row);
+    const uint32_t tile = (uint32_t)xcd_remap(blockIdx.x, gridDim.x), per = (uint32_t)ba.tiles_per_row;
+    const int64_t r = tile / per, tt = tile % per;
     const spd_row_stats st = stats[ba.scope == SPD_SCOPE_ROW ? r : 0];
     boxcar_tile_win<DT, SMALLN, false, UNIT>(pl, vec, r, tt, st, ba, wp, smem);
 }
@@ -125,13 +123,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void b
 // instruction reads 256 consecutive bytes per wave, and sixteen loads per lane
 // are in flight (measured faster than four 16-byte loads per lane, even on
 // aligned rows).  A wave with no SNR at the threshold stops there; the others
-// compact with one ballot per value and one atomic per wave that has
-// candidates.
+// compact with one ballot per value and one atomic per wave.
 __global__ __launch_bounds__(256) void select_kernel(const float* snr, const uint8_t* widx,
                                                      int64_t ncols, int64_t stride, int64_t chunks,
                                                      SelectArgs sa)
 {
-    const int lane = threadIdx.x & 63, tid = threadIdx.x;
+    const int tid = threadIdx.x;
     const uint64_t blk = xcd_remap(blockIdx.x, gridDim.x);
     const int64_t r = (int64_t)(blk / (uint64_t)chunks), ch = (int64_t)(blk % (uint64_t)chunks);
     const float* row = snr + r * stride;
@@ -146,29 +143,24 @@ __global__ __launch_bounds__(256) void select_kernel(const float* snr, const uin
 #pragma unroll
     for (int i = 1; i < 16; ++i) m = fmaxf(m, v[i]);
     if (!__ballot(m >= sa.threshold)) return;                      // the whole wave leaves
+    CandSlots slots;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) slots.add(i, v[i] >= sa.threshold);
+    unsigned long long k = slots.take(sa.cand_count);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        const bool pred = v[i] >= sa.threshold;
-        const uint64_t mask = __ballot(pred);
-        if (!mask) continue;
-        const int cntw = __popcll(mask);
-        const int before = __popcll(mask & ((1ull << lane) - 1ull));
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd((unsigned long long*)sa.cand_count, (unsigned long long)cntw);
-        base = __shfl(base, 0);
-        if (pred) {
-            const unsigned long long k = base + (unsigned long long)before;
-            if (k < (unsigned long long)sa.cand_capacity) {
-                const int64_t t = p0 + 256 * i;
-                spd_candidate cd;
-                cd.row = (int32_t)r;
-                cd.width = sa.width[widx[r * stride + t]];
-                cd.t = t + sa.t_offset;
-                cd.snr = v[i];
-                cd.beam = 0;
-                sa.cand[k] = cd;
-            }
+        if (!slots.has(i)) continue;
+        if (k < (unsigned long long)sa.cand_capacity) {
+            const int64_t t = p0 + 256 * i;
+            spd_candidate cd;
+            cd.row = (int32_t)r;
+            cd.width = sa.width[widx[r * stride + t]];
+            cd.t = t + sa.t_offset;
+            cd.snr = v[i];
+            cd.beam = 0;
+            sa.cand[k] = cd;
         }
+        ++k;
     }
 }
 

@@ -20,10 +20,10 @@ __global__ __launch_bounds__(256) void boxcar_stream_kernel(PlaneArg pl, const s
                                                             WidthPlan wp)
 {
     extern __shared__ float smem[];
-    const uint64_t wg = xcd_remap(blockIdx.x, gridDim.x);
-    const int64_t r = (int64_t)(wg / (uint64_t)ba.tiles_per_row);
+    const uint32_t wg = (uint32_t)xcd_remap(blockIdx.x, gridDim.x), per = (uint32_t)ba.tiles_per_row;
+    const int64_t r = wg / per;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t run = (int64_t)(wg % (uint64_t)ba.tiles_per_row) * (int64_t)(blockDim.x >> 6) + wave;
+    const int64_t run = (int64_t)(wg % per) * (int64_t)(blockDim.x >> 6) + wave;
     const int64_t len = (int64_t)ba.steps * kStreamStep;
     const int64_t t0 = run * len - stream_origin(ba, r);
     if (t0 >= ba.nout) return;
