@@ -426,8 +426,8 @@ def new_candidates(capacity: int, device) -> torch.Tensor:
 
 def candidates_to_numpy(cand: torch.Tensor, count: int) -> np.ndarray:
     n = min(int(count), cand.shape[0])
-    raw = cand[:n].cpu().numpy().tobytes()
-    return np.frombuffer(raw, dtype=CANDIDATE_DTYPE).copy()
+    host = cand[:n].contiguous().cpu() if cand.is_cuda else cand[:n].clone()    # the result's own memory
+    return host.numpy().reshape(-1).view(CANDIDATE_DTYPE)
 
 
 def stats_flags(stats: torch.Tensor) -> torch.Tensor:
