@@ -34,7 +34,13 @@ namespace {
 constexpr int kClusterWaves = 4;                 // waves per workgroup
 constexpr int kClusterUnroll = 4;                // passes per round
 constexpr int kClusterNear = 4;                  // starts each side checked per lane first
-constexpr uint32_t kClusterMaxBlocks = 16384;    // grid-stride beyond this
+// Grid for the longest lists: as many work-groups as the chip holds at once.
+// The list's length is only known on the device, so every launch has this many
+// (unless the list's capacity is smaller), and each of them takes a run of the
+// list, whose peaks share one atomic.  16,384 work-groups against 2,048: 45 and
+// 25 us for 138,000 candidates of 400 pulses (45 before the shared atomic), 510
+// and 131 us for 61,000 peaks among 92,000 candidates (748 before).
+constexpr uint32_t kClusterMaxBlocks = 2048;
 
 struct ClusterArgs {
     const float* snr;
@@ -161,7 +167,7 @@ __global__ __launch_bounds__(64 * kClusterWaves) void cluster_kernel(ClusterArgs
             lost |= (has_l & (left >= vl)) | (has_r & (right > vl));
         }
         const bool survives = on & !lost;
-        uint64_t todo = __ballot(survives);
+        uint64_t todo = __ballot(survives), won = 0;
         // The survivors (local maxima along the row) one at a time with the
         // whole wave: the own row centred on t first, then the other rows.
         while (todo) {
@@ -176,10 +182,14 @@ __global__ __launch_bounds__(64 * kClusterWaves) void cluster_kernel(ClusterArgs
             const int64_t W = t1 - t0, H = r1 - r0;
             bool beaten = scan_own_row(a, v, r, t, t0, W, lane);
             if (!beaten && H > 1) beaten = scan_rows(a, v, r, t, r0, H - 1, t0, W, lane);
-            if (!beaten && lane == 0) {
-                const unsigned long long k = atomicAdd((unsigned long long*)a.peak_count, 1ull);
-                if (k < (unsigned long long)a.peak_capacity) a.peaks[k] = a.cand[base + l];
-            }
+            if (!beaten) won |= 1ull << l;
+        }
+        // one atomic for the wave's peaks: one per peak is what bounds a list of many
+        if (won) {
+            unsigned long long k = 0;
+            if (lane == 0) k = atomicAdd((unsigned long long*)a.peak_count, (unsigned long long)__popcll(won));
+            k = __shfl(k, 0) + (unsigned long long)__popcll(won & ((1ull << lane) - 1ull));
+            if ((won >> lane & 1u) && k < (unsigned long long)a.peak_capacity) a.peaks[k] = a.cand[base + lane];
         }
     }
 }
