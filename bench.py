@@ -122,7 +122,7 @@ def boxcar_kernel_name(workload: str = "ska") -> str:
     form = os.environ.get("SPD_BOXCAR_FORM")
     if form == "strided":
         return "boxcar_kernel"
-    return "boxcar_stream_fast_kernel" if workload == "ska16" and form != "window" else "boxcar_win_kernel"
+    return "boxcar_stream_kernel" if workload == "ska16" and form != "window" else "boxcar_win_kernel"
 
 
 def load_valu(workload: str):
@@ -770,6 +770,9 @@ def run_cluster(args, dev, dm_radius=2, t_radius=256):
 
 
 LDS_PEAK_ADDS = 256 * 128 / 4 * 2 * 2.4e9 / 1e12   # T adds/s: 128 B/clk/CU of LDS reads, 2 adds per 4 B
+# T adds/s of the matrix form: a structured-sparse 16x16x128 int8 product every 16 clocks on each of 4 SIMDs a CU, and
+# each product adds 8 channels to 16 x 16 sums
+MATRIX_PEAK_ADDS = 256 * 4 * 16 * 16 * 8 / 16 * 2.4e9 / 1e12
 
 
 def run_dedisp(args, dev, n_chan=4096, n_samp=1 << 20, n_dm=6000, n_pulses=40):
@@ -855,6 +858,8 @@ def run_dedisp(args, dev, n_chan=4096, n_samp=1 << 20, n_dm=6000, n_pulses=40):
     adds = n_dm * n_chan * n_out
     dd_ms = min(v["dedisp_ms"] for v in out.values())
     tadds = adds / (dd_ms * 1e-3) / 1e12
+    generic = os.environ.get("SPD_DEDISP_FORM") == "generic"
+    peak = LDS_PEAK_ADDS if generic else MATRIX_PEAK_ADDS
     res = {
         "metric": METRIC, "value": a["value"], "unit": "GSamples/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": a["step_ms"], "higher_is_better": True, "scaling": "weak",
@@ -863,10 +868,9 @@ def run_dedisp(args, dev, n_chan=4096, n_samp=1 << 20, n_dm=6000, n_pulses=40):
                    "t_samp_s": band[2], "n_dm": n_dm, "dm_max": round(float(dm[-1]), 2),
                    "max_delay": plan.max_delay, "n_out": n_out, "pulses": n_pulses,
                    "detection": "msd_compute + boxcar_snr, AUTO sigma_N, threshold 7, candidates only"},
-        "roofline": {"bound": "lds", "achieved": round(tadds, 3), "peak": round(LDS_PEAK_ADDS, 2),
-                     "unit": "T adds/s", "frac": round(tadds / LDS_PEAK_ADDS, 4), "traffic": load_traffic("dedisp"),
-                     "kernel": "dedisp_u8_kernel" if os.environ.get("SPD_DEDISP_FORM") == "generic"
-                     else "dedisp_u8_wide_kernel",
+        "roofline": {"bound": "lds" if generic else "matrix", "achieved": round(tadds, 3), "peak": round(peak, 2),
+                     "unit": "T adds/s", "frac": round(tadds / peak, 4), "traffic": load_traffic("dedisp"),
+                     "kernel": "dedisp_u8_kernel" if generic else "dedisp_mfma_kernel",
                      "work_per_launch": "%d additions (trials x channels x starts)" % adds},
         "end_to_end": out,
         "value_note": "value counts de-dispersed samples (trials x starts) per second through the whole step",

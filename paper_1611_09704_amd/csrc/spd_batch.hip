@@ -263,7 +263,8 @@ struct spd_batch_plan {
     int64_t msd_items = 0, tiles[spd::kLayouts] = {0, 0, 0}, units = 0;
     std::vector<spd::BeamDesc> host_beams;
     spd::BeamDesc* d_beams[spd::kLayouts] = {nullptr, nullptr, nullptr};   // tile numbering differs per slot
-    uint32_t* d_beam_of[spd::kLayouts + 1] = {nullptr, nullptr, nullptr, nullptr};   // beam of each tile; last: of each MSD item
+    uint32_t* d_items = nullptr;            // the tables of d_beam_of
+    const uint32_t* d_beam_of[spd::kLayouts + 1] = {};   // beam of each tile; last: of each MSD item
     double* d_part = nullptr;
     spd_row_stats* d_stats = nullptr;
     int64_t* d_counters = nullptr;          // [0] boxcar queue, [1] scratch count
@@ -471,19 +472,18 @@ static void cache_store(const std::string& key, const Schedule& sc)
 
 using namespace spd;
 
-// One byte per item: items [start(b), start(b + 1)) belong to beam b.
-static hipError_t upload_beam_of(int64_t total, const std::vector<BeamDesc>& v, int64_t BeamDesc::* start, uint32_t** out)
+// Appends a table of one byte per item to `words`: items [start(b), start(b + 1)) belong to beam b.
+static size_t add_beam_of(int64_t total, const std::vector<BeamDesc>& v, int64_t BeamDesc::* start,
+                          std::vector<uint32_t>& words)
 {
-    std::vector<uint32_t> words((size_t)((total + 3) / 4), 0);
-    uint8_t* t = (uint8_t*)words.data();
+    const size_t at = words.size();
+    words.resize(at + (size_t)(total + 3) / 4, 0);
+    uint8_t* t = (uint8_t*)(words.data() + at);
     for (size_t b = 0; b < v.size(); ++b) {
         const int64_t i0 = v[b].*start, i1 = b + 1 < v.size() ? v[b + 1].*start : total;
-        memset(t + i0, (int)b, (size_t)(i1 - i0));
+        if (i1 > i0) memset(t + i0, (int)b, (size_t)(i1 - i0));
     }
-    const size_t bytes = std::max<size_t>(words.size(), 1) * 4;
-    hipError_t e = hipMalloc((void**)out, bytes);
-    if (e == hipSuccess && !words.empty()) e = hipMemcpy(*out, words.data(), words.size() * 4, hipMemcpyHostToDevice);
-    return e;
+    return at;
 }
 
 static spd_status build_beams(spd_batch_plan* P, const spd_plane* beams)
@@ -506,6 +506,9 @@ static spd_status build_beams(spd_batch_plan* P, const spd_plane* beams)
     }
     P->msd_items = msd;
     P->units = units;
+    constexpr size_t kNone = (size_t)-1;
+    std::vector<uint32_t> words;                           // the beam tables, uploaded together
+    size_t at[kLayouts + 1] = {kNone, kNone, kNone, kNone};
     for (int k = 0; k < kLayouts; ++k) {
         if (k == 2 && !P->has_win) continue;
         const int X = k ? 8 : 4;
@@ -523,15 +526,20 @@ static spd_status build_beams(spd_batch_plan* P, const spd_plane* beams)
         e = hipMemcpy(P->d_beams[k], v.data(), sizeof(BeamDesc) * P->n_beams, hipMemcpyHostToDevice);
         if (e != hipSuccess) return device_status(e, "hipMemcpy(beams)");
         // the grid launch's; more tiles than one grid holds take the persistent form
-        if ((uint64_t)t * 64u * (uint64_t)P->max_waves[k] <= kMaxGridItems &&
-            (e = upload_beam_of(t, v, &BeamDesc::tile_start, &P->d_beam_of[k])) != hipSuccess)
-            return device_status(e, "tile table");
+        if ((uint64_t)t * 64u * (uint64_t)P->max_waves[k] <= kMaxGridItems)
+            at[k] = add_beam_of(t, v, &BeamDesc::tile_start, words);
     }
     for (int k = 0; k < kLayouts; ++k) P->tiles[k] = tiles[k];
     if (P->units > 0x7fffffffLL || P->msd_items > 0x7fffffffLL)
         return fail(SPD_E_UNSUPPORTED, "batch too large");
-    hipError_t e = upload_beam_of(msd, P->host_beams, &BeamDesc::msd_start, &P->d_beam_of[kLayouts]);
-    if (e != hipSuccess) return device_status(e, "item table");
+    at[kLayouts] = add_beam_of(msd, P->host_beams, &BeamDesc::msd_start, words);
+    const size_t bytes = words.size() * sizeof(uint32_t);
+    hipError_t e = hipMalloc((void**)&P->d_items, bytes);
+    if (e != hipSuccess) return device_status(e, "hipMalloc(items)");
+    if ((e = hipMemcpy(P->d_items, words.data(), bytes, hipMemcpyHostToDevice)) != hipSuccess)
+        return device_status(e, "hipMemcpy(items)");
+    for (int k = 0; k <= kLayouts; ++k)
+        if (at[k] != kNone) P->d_beam_of[k] = P->d_items + at[k];
     return SPD_OK;
 }
 
@@ -773,8 +781,7 @@ void spd_batch_plan_destroy(spd_batch_plan* P)
         if (P->d_beams[k]) hipFree(P->d_beams[k]);
     if (P->d_part) hipFree(P->d_part);
     if (P->d_stats) hipFree(P->d_stats);
-    for (uint32_t* t : P->d_beam_of)
-        if (t) hipFree(t);
+    if (P->d_items) hipFree(P->d_items);
     if (P->d_counters) hipFree(P->d_counters);
     delete P;
 }

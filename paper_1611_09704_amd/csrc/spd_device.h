@@ -3,7 +3,7 @@
 // (spd_batch.hip).  Library-internal.
 //
 //   msd_block_x / msd_block_xy   per-(row, column block) partials, Sec. 2.1
-//   finalize_unit                FP64 merge across blocks, sigma_N, Sec. 2.1-2.2
+//   finalize_unit(_lanes)        FP64 merge across blocks, sigma_N, Sec. 2.1-2.2
 //   boxcar_tile                  boxcars, SNR, highest SNR and its first width,
 //                                fused threshold; Sec. 2.3 / Algorithm 1, Sec. 2.4
 //   boxcar_tile_win              the same for width lists of stepped groups,
@@ -1292,7 +1292,7 @@ __device__ __forceinline__ float4 cvt4(const Loader<DT>& ld, typename RawT<DT>::
 // running sums in the same order, and the same first-maximiser rule.
 // UNIT: every group steps by 1 (the lists 1..8k), so no step is chosen per
 // group and the winner's sums are remade from one read per width, not two
-// (79 VGPRs instead of 128: 6 waves per SIMD instead of 4).
+// (74 VGPRs instead of 125: 6 waves per SIMD instead of 4).
 
 template <int DT, int SMALLN, bool DIT = false, bool UNIT = false>
 __device__ void boxcar_tile_win(const PlaneArg& pl, bool vec, int64_t r, int64_t tt, const spd_row_stats& st,

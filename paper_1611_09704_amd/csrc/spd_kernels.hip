@@ -1,7 +1,7 @@
 // spd_kernels.hip -- one-plane launches of the detection path on gfx950.
 //
 //   msd_x_kernel / msd_xy_kernel   per-block (n, T, S) partials, Sec. 2.1
-//   msd_finalize_kernel            FP64 merge across blocks and sigma_N
+//   msd_finalize(_lanes)_kernel    FP64 merge across blocks and sigma_N
 //                                  coefficients, Sec. 2.1-2.2
 //   boxcar_kernel                  boxcars, SNR, highest SNR and its width,
 //                                  fused threshold, Sec. 2.3 / Algorithm 1,
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void boxcar_kernel(PlaneArg pl, bool vec, cons
 // sum plus two groups' windows; capping it at 128 VGPRs keeps 4 waves per SIMD
 // without spills (uncapped it takes 132 and drops to 3).  The lists that step by
 // 1 throughout (1..24, 1..32, ...) have a variant of their own without the
-// step's choice: 79 VGPRs, 6 waves per SIMD.  Bound by the vector units (two
+// step's choice: 74 VGPRs, 6 waves per SIMD.  Bound by the vector units (two
 // instructions per start and width); with the window's loads in flight before
 // the tables are made, at any alignment of the rows: U8 1024 x 262144, 1..64,
 // 1,524 -> 1,276 us on contiguous rows; F32 1024 x 262144, 1..32, 1,266 -> 902 us

@@ -120,8 +120,10 @@ def _short(name: str, with_args: bool = False) -> str:
     if with_args and "<" in name.split("(")[0]:
         targs = "<" + name.split("(")[0].split("<", 1)[1]
     for key in ("batch_boxcar_win_grid_kernel", "batch_boxcar_grid_kernel", "batch_boxcar_kernel", "batch_msd_kernel",
-                "batch_finalize_kernel", "boxcar_dit_kernel", "boxcar_stream_fast_kernel", "boxcar_stream_kernel", "boxcar_win_kernel", "boxcar_kernel", "msd_xy_kernel", "msd_x_kernel", "msd_finalize_kernel",
-                "select_kernel", "cluster_kernel", "dedisp_u8_wide_kernel", "dedisp_u8_kernel",
+                "batch_finalize_kernel", "batch_finalize_lanes_kernel", "boxcar_dit_kernel", "boxcar_stream_kernel",
+                "boxcar_win_kernel", "boxcar_kernel", "msd_xy_kernel", "msd_x_kernel", "msd_finalize_kernel",
+                "msd_finalize_lanes_kernel", "select_kernel", "cluster_kernel", "dedisp_mfma_kernel",
+                "dedisp_u8_wide_kernel", "dedisp_u8_kernel",
                 "fill_i64_kernel"):
         if key in name:
             return key + targs
@@ -228,10 +230,10 @@ def summarize(args):
             d["cluster"] = {"kernel_sha": sha, **traffic.get("cluster_kernel", {})}
         elif args.workload == "dedisp":
             d["dedisp"] = {"kernel_sha": sha,
-                           **(traffic.get("dedisp_u8_wide_kernel") or traffic.get("dedisp_u8_kernel") or {})}
+                           **(traffic.get("dedisp_mfma_kernel") or traffic.get("dedisp_u8_wide_kernel")
+                              or traffic.get("dedisp_u8_kernel") or {})}
         else:
-            box = (traffic.get("boxcar_dit_kernel") or traffic.get("boxcar_stream_fast_kernel")
-                   or traffic.get("boxcar_stream_kernel")
+            box = (traffic.get("boxcar_dit_kernel") or traffic.get("boxcar_stream_kernel")
                    or traffic.get("boxcar_win_kernel") or traffic.get("boxcar_kernel") or {})
             d[args.workload] = {"kernel_sha": sha, **box,
                                 "msd": traffic.get("msd_xy_kernel") or traffic.get("msd_x_kernel")}
