@@ -298,7 +298,7 @@ spd_status plan_boxcar(const spd_plane* x, const spd_params* p, const spd_row_st
         bp.wp.win = 4;
         bp.waves = 4;
         // the launch takes long enough runs for any plane up to this size
-        const int64_t wg = (int64_t)bp.waves * kStreamStepsMax * kStreamStep;
+        const int64_t wg = (int64_t)bp.waves * kStreamPlanSteps * kStreamStep;
         ba.tiles_per_row = (nout + wg - 1) / wg;
     }
     ba.snr = snr_out;

@@ -1811,6 +1811,7 @@ __device__ __forceinline__ void short_coefs(const spd_row_stats& st, float (&a)[
 // SNR array (or 16-byte boundary of the width indices), in starts.
 __device__ __forceinline__ int stream_origin(const BoxcarArgs& ba, int64_t r)
 {
+    if (!ba.aligned) return 0;
     const uint64_t at = (uint64_t)(r * ba.out_stride) +
                         (ba.snr ? (uint64_t)(uintptr_t)ba.snr / 4 : (uint64_t)(uintptr_t)ba.widx);
     return ba.snr || ba.widx ? (int)(at & 15) : 0;
@@ -1886,9 +1887,12 @@ __device__ __forceinline__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, i
 }
 
 // Any run: the valid starts among S steps from t_begin (which may lie before
-// the row) of row r by one wave.  Steps inside the row load 4 samples at a
-// time, others are checked sample by sample; whole steps store vectors where
-// the outputs allow it, others per element.  buf is the wave's 2*kStreamBuf
+// the row) of row r by one wave.  A lane whose 4 samples lie inside the row
+// loads them together and one whose 4 starts are valid stores them together,
+// at whatever alignment; only the lanes on a row's edges go element by element
+// (with whole steps as the condition, rows of 600 starts, in two steps of which
+// at most one is whole, were 1.1 to 1.6 times slower).  The loads are ordinary
+// ones: past the caches, planes that fit them took 1.3 to 1.5 times as long.  buf is the wave's 2*kStreamBuf
 // floats of LDS (16-byte aligned).
 template <int DT, int N>
 __device__ __forceinline__ void boxcar_run_short(const PlaneArg& pl, int64_t r, int64_t t_begin, const spd_row_stats& st,
@@ -1907,9 +1911,9 @@ __device__ __forceinline__ void boxcar_run_short(const PlaneArg& pl, int64_t r, 
     const int64_t ncols = pl.n_cols;
     const int lo = 4 * lane;
     auto load = [&](int step, int at) -> Raw {              // at: 0 or 256
-        const int64_t t = t_begin + (int64_t)step * kStreamStep;
-        if (t >= 0 && t + kStreamStep <= ncols) return raw4_any<DT, true>(ld, t + at + lo);   // uniform
-        return raw4<DT>(ld, t + at + lo, ncols);
+        const int64_t c = t_begin + (int64_t)step * kStreamStep + at + lo;
+        if (c >= 0 && c + 3 < ncols) return raw4_any<DT>(ld, c);
+        return raw4<DT>(ld, c, ncols);
     };
 
     float* A = buf;
@@ -1931,7 +1935,8 @@ __device__ __forceinline__ void boxcar_run_short(const PlaneArg& pl, int64_t r, 
 
     float* so = ba.snr ? ba.snr + r * ba.out_stride + t_begin : nullptr;
     uint8_t* wo = ba.widx ? ba.widx + r * ba.out_stride + t_begin : nullptr;
-    const bool vs = ((uintptr_t)so & 15) == 0, vw = ((uintptr_t)wo & 3) == 0;
+    typedef f32x4 SnrAny __attribute__((aligned(4)));
+    typedef uint32_t IdxAny __attribute__((aligned(1)));
     for (int k = 0; k < steps; ++k) {
         const int ks = k * kStreamStep;
         if (k + 1 < steps) {
@@ -1959,15 +1964,16 @@ __device__ __forceinline__ void boxcar_run_short(const PlaneArg& pl, int64_t r, 
             }
             if (ba.cand && __ballot(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])) >= ba.threshold))
                 emit_block_cands(ba, wp, r, t_begin + off, first, cnt, sv, pk);
-            if (whole && vs && so) {
-                *(float4*)(so + off) = make_float4(sv[0], sv[1], sv[2], sv[3]);
+            const bool all = first == 0 && cnt == 4;
+            if (so && all) {
+                *(SnrAny*)(so + off) = f32x4{sv[0], sv[1], sv[2], sv[3]};
             } else if (so) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
                     if (i >= first && i < cnt) so[off + i] = sv[i];
             }
-            if (whole && vw && wo) {
-                *(uint32_t*)(wo + off) = pk;
+            if (wo && all) {
+                *(IdxAny*)(wo + off) = pk;
             } else if (wo) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "spd.h"
+#include "spd_sched.h"
 
 namespace spd {
 
@@ -20,13 +21,11 @@ constexpr int kWinX = 8;           // consecutive starts per lane in the registe
 constexpr int kSelCols = 4096;     // columns per work-group of the standalone threshold (16 per lane)
 constexpr int kWinTableFloats = (kMaxWidthsPadded + 2 * kMaxGroups + 63) / 64 * 64;
 
-// Streaming form of the short lists 1..n (n <= 16): a wave walks a run of a
-// few steps of kStreamStep consecutive starts of one row; lane l
-// takes starts 4l..4l+3 and 256+4l..256+4l+3 of each step.  Its LDS holds two
-// buffers of one step's samples plus the next 16.
-constexpr int kStreamStep = 512;
-constexpr int kStreamSteps = 8;         // of an ordinary launch; doubled where the grid would not hold the runs
-constexpr int kStreamStepsMax = 16;
+// Streaming form: lane l takes starts 4l..4l+3 and 256+4l..256+4l+3 of each
+// step.  A wave's LDS holds two buffers of one step's samples plus the next 16.
+// A plane whose runs of kStreamPlanSteps steps fit one launch is taken; the
+// launch picks its own run length (stream_shape).
+constexpr int kStreamPlanSteps = 16;
 constexpr int kStreamBuf = kStreamStep + 16;
 
 // Register-window form: logical element m of a wave's LDS array is stored at
@@ -52,7 +51,6 @@ __host__ __device__ constexpr int dit_level_floats(int levels, int lv)
 // LDS floats of the boxcar kernel's coefficient and step tables, rounded up so
 // the per-wave arrays after them start on a 256-byte boundary.
 constexpr int kTableFloats = (3 * kMaxWidthsPadded + 63) / 64 * 64;
-constexpr uint64_t kMaxGridItems = 0xffffffffull;   // work-items per launch (1-D grid)
 
 // How each width's boxcar is reached from the previous one:
 //   B_{w_i}(t) = B_{w_{i-1}}(t) + sum_{m < cnt_i} D_{g}[t + off_i + m*g]
@@ -105,6 +103,7 @@ struct BoxcarArgs {
     uint32_t beam;          // stored in each candidate (batched runs)
     uint32_t out_vec;       // bit 0: snr rows allow 16-byte stores; bit 1: widx rows allow 8-byte stores
     int32_t steps;          // streaming form: steps per run
+    int32_t aligned;        // streaming form: steps on the outputs' 64-byte boundaries
 };
 
 struct SelectArgs {

@@ -15,7 +15,7 @@ hipError_t launch_boxcar(int dtype, const PlaneArg& pl, bool vec, const spd_row_
                          const BoxcarArgs& ba, const WidthPlan& wp, int X, int waves, uint64_t ntiles,
                          hipStream_t s);
 hipError_t launch_stream(int dtype, const PlaneArg& pl, const spd_row_stats* stats, const BoxcarArgs& ba,
-                         const WidthPlan& wp, int waves, hipStream_t s);
+                         const WidthPlan& wp, hipStream_t s);
 hipError_t launch_zero_count(int64_t* count, hipStream_t s);
 hipError_t launch_fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s);
 hipError_t launch_select(const float* snr, const uint8_t* widx, int64_t nrows, int64_t ncols,

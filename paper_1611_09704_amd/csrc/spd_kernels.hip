@@ -229,7 +229,7 @@ static hipError_t launch_boxcar_dt(const PlaneArg& pl, bool vec, const spd_row_s
     const size_t lds = boxcar_lds_bytes(waves, ba, wp.win != 0);   // <= 64 KiB by construction of the plan
     constexpr int X = kOutPerLane;
     if (wp.win == 4)
-        return launch_stream(DT, pl, stats, ba, wp, waves, s);
+        return launch_stream(DT, pl, stats, ba, wp, s);
     if (wp.win == 3)
         hipLaunchKernelGGL((boxcar_dit_kernel<DT>), dim3(ntiles), dim3(64 * waves), lds, s, pl, vec, stats, ba, wp);
     else if (wp.win == 1 && wp.win_unit)

@@ -1,11 +1,53 @@
-// spd_sched.h -- the host rule that decides whether a batched-run schedule
-// read from the tuning cache can run a given plan.  Plain C++ (no HIP types),
-// so the rule is also compiled and checked on its own on the host.
+// spd_sched.h -- host rules of the launches: whether a batched-run schedule
+// read from the tuning cache can run a given plan, and how the streaming form
+// cuts its rows.  Plain C++ (no HIP types), so the rules are also compiled and
+// checked on their own on the host.
 #pragma once
 
 #include <stdint.h>
 
 namespace spd {
+
+constexpr uint64_t kMaxGridItems = 0xffffffffull;   // work-items per launch (1-D grid)
+
+// Streaming form of the short lists 1..n (n <= 16): a wave walks a run of a
+// few steps of kStreamStep consecutive starts of one row.
+constexpr int kStreamStep = 512;
+
+struct StreamShape {
+    int steps;              // steps per run (2 or more)
+    int waves;              // runs, and waves, per work-group
+    int64_t tiles_per_row;  // work-groups per row
+    bool aligned;           // the steps lie on 64-byte boundaries of the outputs, so that the first of a row begins
+                            // up to 15 starts before it
+};
+
+// Long runs amortise a wave's start (coefficients, first loads), short ones give small planes enough waves:
+// 8 steps against 4 and 2 take 1582, 1644 and 1756 us on 2,048 x 524,281 U8 (262,000 waves), 38.6,
+// 38.3 and 36.0 on 256 x 65,536 F32, 19.1, 14.7 and 13.1 on 64 x 65,536 F32 (30.2 with 16).
+//
+// Rows of fewer than 4 steps are walked from their first start: on the boundaries of the outputs they may take a
+// step more (F32, list 1..1, 39,603 x 505: 38.7 us, 29.9 from the first start; 6,664 x 3,001 29.7 and 31.8; U8
+// 29.5 and 24.0 on 13,324 x 1,501, 22.6 and 25.0 on 4,900 x 4,081).
+//
+// A work-group has no more waves than a row has runs: with 4 for rows of one run, three of them ended at once and
+// the planes of many short rows were bound by starting them (200,000 x 107 F32, 1..8: 294 us, 157 with one).
+inline StreamShape stream_shape(int64_t n_rows, int64_t nout)
+{
+    StreamShape f;
+    f.aligned = nout >= 4 * kStreamStep;
+    const int64_t steps = (nout + (f.aligned ? 15 : 0) + kStreamStep - 1) / kStreamStep;   // of any row
+    auto runs = [&](int64_t per) { return (steps + per - 1) / per; };
+    f.steps = n_rows * runs(8) >= 32768 ? 8 : n_rows * runs(4) >= 16384 ? 4 : 2;
+    for (;; f.steps *= 2) {
+        f.waves = runs(f.steps) < 4 ? (int)runs(f.steps) : 4;
+        f.tiles_per_row = (runs(f.steps) + f.waves - 1) / f.waves;
+        // one run per row always fits: the caller's rows are at most kMaxGridItems / 256
+        if ((uint64_t)n_rows * (uint64_t)f.tiles_per_row * 64u * (uint64_t)f.waves <= kMaxGridItems || runs(f.steps) == 1)
+            break;
+    }
+    return f;
+}
 
 // A cached schedule (outputs per lane X, register-window form `win`,
 // persistent work-groups per CU, tiles per queue grab) is usable for a plan

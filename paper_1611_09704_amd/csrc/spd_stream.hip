@@ -3,13 +3,11 @@
 // 2.4).  The arithmetic lives in spd_device.h (boxcar_run_fast,
 // boxcar_run_short).
 //
-// Each row's starts are cut into runs of `steps` steps, one wave per run, four
-// runs per work-group.  A run that lies wholly inside its row (every start
+// Each row's starts are cut into runs of `steps` steps, one wave per run, up to
+// four runs per work-group (stream_shape).  A run that lies wholly inside its row (every start
 // valid, every sample it reads inside the row), with both outputs on vector
 // boundaries or none at all, takes boxcar_run_fast; the others (each row's
 // first and last run) boxcar_run_short.
-#include <algorithm>
-
 #include "spd_device.h"
 #include "spd_kernels.h"
 
@@ -51,21 +49,16 @@ static hipError_t launch_n(const PlaneArg& pl, const spd_row_stats* stats, const
 }
 
 hipError_t launch_stream(int dtype, const PlaneArg& pl, const spd_row_stats* stats, const BoxcarArgs& ba0,
-                         const WidthPlan& wp, int waves, hipStream_t s)
+                         const WidthPlan& wp, hipStream_t s)
 {
     if (wp.n < 1 || wp.n > 16) return hipErrorInvalidValue;
+    const StreamShape f = stream_shape(pl.n_rows, ba0.nout);
+    const int waves = f.waves;
     const size_t lds = (size_t)waves * 2 * kStreamBuf * sizeof(float);
     BoxcarArgs ba = ba0;
-    const int64_t steps = (ba.nout + 15 + kStreamStep - 1) / kStreamStep;   // of any row
-    // Long runs amortise a wave's start (coefficients, first loads), short ones give small planes enough waves:
-    // 8 steps against 4 and 2 take 1582, 1644 and 1756 us on 2,048 x 524,281 U8 (262,000 waves), 38.6,
-    // 38.3 and 36.0 on 256 x 65,536 F32, 19.1, 14.7 and 13.1 on 64 x 65,536 F32 (30.2 with 16).
-    auto wave_count = [&](int64_t per) { return pl.n_rows * ((steps + per - 1) / per); };
-    ba.steps = wave_count(kStreamSteps) >= 32768 ? kStreamSteps : wave_count(kStreamSteps / 2) >= 16384 ? kStreamSteps / 2
-                                                                                                       : kStreamSteps / 4;
-    auto tiles = [&](int64_t per) { return ((steps + per - 1) / per + waves - 1) / waves; };   // per row
-    while ((uint64_t)pl.n_rows * (uint64_t)tiles(ba.steps) * 64u * (uint64_t)waves > kMaxGridItems) ba.steps *= 2;
-    ba.tiles_per_row = tiles(ba.steps);
+    ba.steps = f.steps;
+    ba.aligned = f.aligned;
+    ba.tiles_per_row = f.tiles_per_row;
     // 16-byte SNR stores and 4-byte width-index stores on one grid of starts
     const bool out = ba.snr && ba.widx && (((uintptr_t)ba.snr / 4 - (uintptr_t)ba.widx) & 3) == 0;
     const uint64_t grid = (uint64_t)pl.n_rows * (uint64_t)ba.tiles_per_row;
