@@ -1838,19 +1838,28 @@ __device__ __forceinline__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, i
     float* so = OUT ? ba.snr + r * ba.out_stride + t_begin + lo : nullptr;
     uint8_t* wo = OUT ? ba.widx + r * ba.out_stride + t_begin + lo : nullptr;
 
+    const bool once = ba.once != 0;
+    auto load = [&](int64_t at) -> Raw {
+        if (!once) return raw4_any<DT>(ld, at);
+        asm volatile("");                                   // kept apart: merged, both loads would be ordinary
+        const Raw v = raw4_any<DT, true>(ld, at);
+        asm volatile("");
+        return v;
+    };
+
     float* A = buf;
     float* Bv = buf + kStreamBuf;
     {
-        const Raw s0 = raw4_any<DT, true>(ld, c), s1 = raw4_any<DT, true>(ld, c + 256);
+        const Raw s0 = load(c), s1 = load(c + 256);
         put_shifted(A + lo, cvt4<DT>(ld, s0), mu_hi, mu_lo);
         put_shifted(A + 256 + lo, cvt4<DT>(ld, s1), mu_hi, mu_lo);
     }
     Raw r0{}, r1{};
     if (S > 1) {
-        r0 = raw4_any<DT, true>(ld, c + kStreamStep);
-        r1 = raw4_any<DT, true>(ld, c + kStreamStep + 256);
+        r0 = load(c + kStreamStep);
+        r1 = load(c + kStreamStep + 256);
     } else if (lane < 4) {
-        r0 = raw4_any<DT, true>(ld, c + kStreamStep);
+        r0 = load(c + kStreamStep);
     }
     if (lane < 4) put_shifted(A + kStreamStep + lo, cvt4<DT>(ld, r0), mu_hi, mu_lo);
     wave_sync();
@@ -1861,10 +1870,10 @@ __device__ __forceinline__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, i
         }
         const int64_t nx = c + (k + 2) * kStreamStep;
         if (k + 2 < S) {
-            r0 = raw4_any<DT, true>(ld, nx);
-            r1 = raw4_any<DT, true>(ld, nx + 256);
+            r0 = load(nx);
+            r1 = load(nx + 256);
         } else if (k + 2 == S && lane < 4) {
-            r0 = raw4_any<DT, true>(ld, nx);
+            r0 = load(nx);
         }
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {

@@ -67,4 +67,10 @@ inline bool schedule_usable(int X, int win, int wgs_per_cu, int grab, bool has_w
     return true;
 }
 
+// The streaming form loads samples past the caches (nontemporal) where the plane is larger than the 256 MB
+// memory-side cache; a smaller one may still be there from the statistics pass or the call before.  F32 with both
+// outputs, past the caches and not: 128 MB, 1..1 65 and 46 us; 256 MB, 1..16 120 and 110; 320 MB 137 and 139; 2 GB
+// 871 and 891.  F16, candidates only, 1..8: 192 MB 76 and 69, 400 MB 146 and 149.
+inline bool stream_once(int64_t plane_bytes) { return plane_bytes > (int64_t)256 << 20; }
+
 }  // namespace spd

@@ -58,6 +58,7 @@ hipError_t launch_stream(int dtype, const PlaneArg& pl, const spd_row_stats* sta
     BoxcarArgs ba = ba0;
     ba.steps = f.steps;
     ba.aligned = f.aligned;
+    ba.once = stream_once(pl.n_rows * pl.n_cols * (dtype == SPD_F32 ? 4 : dtype == SPD_F16 ? 2 : 1));
     ba.tiles_per_row = f.tiles_per_row;
     // 16-byte SNR stores and 4-byte width-index stores on one grid of starts
     const bool out = ba.snr && ba.widx && (((uintptr_t)ba.snr / 4 - (uintptr_t)ba.widx) & 3) == 0;

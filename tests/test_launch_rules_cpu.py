@@ -27,6 +27,9 @@ int main()
             get(2);
             const spd::StreamShape f = spd::stream_shape(v[0], v[1]);
             std::printf("%d %d %lld %d\n", f.steps, f.waves, (long long)f.tiles_per_row, (int)f.aligned);
+        } else if (!std::strcmp(name, "stream_once")) {
+            get(1);
+            std::printf("%d\n", (int)spd::stream_once(v[0]));
         } else {
             return 3;
         }
@@ -79,3 +82,8 @@ def test_stream_shape_covers_every_row_and_fits_a_launch(rule):
         assert s >= 2 and 1 <= w <= 4
         assert tiles * w * s * 512 >= n + 15 * a
         assert r * tiles * w * 64 <= MAX_ITEMS
+
+
+@pytest.mark.parametrize("mb,once", [(32, 0), (128, 0), (192, 0), (256, 0), (320, 1), (400, 1), (2048, 1)])
+def test_stream_loads_past_the_caches_only_from_planes_they_cannot_hold(rule, mb, once):
+    assert rule([("stream_once", mb << 20)]) == [(once,)]
