@@ -24,7 +24,9 @@ struct StreamShape {
 
 // Long runs amortise a wave's start (coefficients, first loads), short ones give small planes enough waves:
 // 8 steps against 4 and 2 take 1582, 1644 and 1756 us on 2,048 x 524,281 U8 (262,000 waves), 38.6,
-// 38.3 and 36.0 on 256 x 65,536 F32, 19.1, 14.7 and 13.1 on 64 x 65,536 F32 (30.2 with 16).
+// 38.3 and 36.0 on 256 x 65,536 F32, 19.1, 14.7 and 13.1 on 64 x 65,536 F32 (30.2 with 16).  Without outputs
+// (candidates only) a step is shorter, and 16 steps are better than 8 where they still give 32,768 waves
+// (2,048 x 262,144, 1..8, F16 355 and 363 us, 1..16, U8 562 and 576; with U8 outputs, 1..8, 612 and 602).
 //
 // Rows of fewer than 4 steps are walked from their first start: on the boundaries of the outputs they may take a
 // step more (F32, list 1..1, 39,603 x 505: 38.7 us, 29.9 from the first start; 6,664 x 3,001 29.7 and 31.8; U8
@@ -32,13 +34,16 @@ struct StreamShape {
 //
 // A work-group has no more waves than a row has runs: with 4 for rows of one run, three of them ended at once and
 // the planes of many short rows were bound by starting them (200,000 x 107 F32, 1..8: 294 us, 157 with one).
-inline StreamShape stream_shape(int64_t n_rows, int64_t nout)
+inline StreamShape stream_shape(int64_t n_rows, int64_t nout, bool outputs)
 {
     StreamShape f;
     f.aligned = nout >= 4 * kStreamStep;
     const int64_t steps = (nout + (f.aligned ? 15 : 0) + kStreamStep - 1) / kStreamStep;   // of any row
     auto runs = [&](int64_t per) { return (steps + per - 1) / per; };
-    f.steps = n_rows * runs(8) >= 32768 ? 8 : n_rows * runs(4) >= 16384 ? 4 : 2;
+    f.steps = !outputs && n_rows * runs(16) >= 32768 ? 16
+              : n_rows * runs(8) >= 32768            ? 8
+              : n_rows * runs(4) >= 16384            ? 4
+                                                     : 2;
     for (;; f.steps *= 2) {
         f.waves = runs(f.steps) < 4 ? (int)runs(f.steps) : 4;
         f.tiles_per_row = (runs(f.steps) + f.waves - 1) / f.waves;

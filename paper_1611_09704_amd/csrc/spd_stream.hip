@@ -52,7 +52,7 @@ hipError_t launch_stream(int dtype, const PlaneArg& pl, const spd_row_stats* sta
                          const WidthPlan& wp, hipStream_t s)
 {
     if (wp.n < 1 || wp.n > 16) return hipErrorInvalidValue;
-    const StreamShape f = stream_shape(pl.n_rows, ba0.nout);
+    const StreamShape f = stream_shape(pl.n_rows, ba0.nout, ba0.snr || ba0.widx);
     const int waves = f.waves;
     const size_t lds = (size_t)waves * 2 * kStreamBuf * sizeof(float);
     BoxcarArgs ba = ba0;

@@ -55,3 +55,24 @@ def test_short_rows(nout, col0, wcol0, snr, widx):
     assert len(got[2]) > 0 or nout < 512
     for f in ("row", "t", "width", "snr"):
         assert np.array_equal(got[2][f], want[2][f])
+
+
+def test_long_runs():
+    """Candidates only, on enough rows for runs of 16 steps."""
+    x = torch.randn((6144, 49153), generator=torch.Generator(device=DEV).manual_seed(1), device=DEV).to(torch.float16)
+    p = B.Params(list(range(1, 9)), 6.0)
+    st = B.msd_compute(x, p)
+    print("case: long runs", flush=True)
+    got = []
+    for form in ("", "window"):
+        os.environ["SPD_BOXCAR_FORM"] = form
+        try:
+            cand, count = B.new_candidates(1 << 16, DEV), torch.zeros(1, dtype=torch.int64, device=DEV)
+            B.boxcar_snr(x, p, st, cand=cand, cand_count=count)
+            c = B.candidates_to_numpy(cand, int(count.item()))
+            got.append(c[np.lexsort((c["t"], c["row"]))])
+        finally:
+            del os.environ["SPD_BOXCAR_FORM"]
+    assert len(got[0]) > 0
+    for f in ("row", "t", "width", "snr"):
+        assert np.array_equal(got[0][f], got[1][f])

@@ -24,8 +24,8 @@ int main()
     while (std::scanf("%63s", name) == 1) {
         auto get = [&](int n) { for (int i = 0; i < n; ++i) if (std::scanf("%lld", v + i) != 1) std::exit(2); };
         if (!std::strcmp(name, "stream_shape")) {
-            get(2);
-            const spd::StreamShape f = spd::stream_shape(v[0], v[1]);
+            get(3);
+            const spd::StreamShape f = spd::stream_shape(v[0], v[1], v[2] != 0);
             std::printf("%d %d %lld %d\n", f.steps, f.waves, (long long)f.tiles_per_row, (int)f.aligned);
         } else if (!std::strcmp(name, "stream_once")) {
             get(1);
@@ -67,18 +67,24 @@ def rule(tmp_path_factory):
     (2048, 524266, 8, 4, 1),
 ])
 def test_stream_shape(rule, rows, nout, steps, waves, aligned):
-    (s, w, tiles, a), = rule([("stream_shape", rows, nout)])
+    (s, w, tiles, a), = rule([("stream_shape", rows, nout, 1)])
     assert (s, w, a) == (steps, waves, aligned)
     runs = -(-(-(-(nout + 15 * a) // 512)) // s)
     assert tiles == -(-runs // w)
+
+
+@pytest.mark.parametrize("rows,nout,outputs,steps", [(2048, 262000, 1, 8), (2048, 262000, 0, 16),
+                                                     (1024, 262000, 0, 16), (1023, 262000, 0, 8)])
+def test_stream_runs_are_longer_without_outputs(rule, rows, nout, outputs, steps):
+    assert rule([("stream_shape", rows, nout, outputs)])[0][0] == steps
 
 
 def test_stream_shape_covers_every_row_and_fits_a_launch(rule):
     rng = random.Random(5)
     cases = [(1, 1 << 40), (1 << 24, 1), (1 << 24, 512), (1 << 24, 9000), (16776960, 32768 * 1), (1 << 23, 70000)]
     cases += [(int(2 ** rng.uniform(0, 22)), int(2 ** rng.uniform(0, 30))) for _ in range(400)]
-    cases = [(r, n) for r, n in cases if r * -(-n // (4 * 16 * 512)) * 256 <= MAX_ITEMS]     # what a plan takes
-    for (r, n), (s, w, tiles, a) in zip(cases, rule([("stream_shape",) + c for c in cases])):
+    cases = [(r, n, len(str(n)) % 2) for r, n in cases if r * -(-n // (4 * 16 * 512)) * 256 <= MAX_ITEMS]     # what a plan takes
+    for (r, n, _), (s, w, tiles, a) in zip(cases, rule([("stream_shape",) + c for c in cases])):
         assert s >= 2 and 1 <= w <= 4
         assert tiles * w * s * 512 >= n + 15 * a
         assert r * tiles * w * 64 <= MAX_ITEMS
