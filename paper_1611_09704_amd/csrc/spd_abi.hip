@@ -118,15 +118,15 @@ MsdLayout msd_layout(const spd_plane* x)
 // The register-window form of the boxcar kernel (8 consecutive starts per
 // lane): used for the list 1..n with n <= 16, and for lists of groups of 8
 // unit-count widths (the last may be shorter) that each step by 1 or 2 through
-// one array from an offset that is a multiple of 8.  It beats the strided form
-// for all of them: F32 1,024 x 131,072, lists 1..n, strided -> window: n = 17 610
-// -> 432 us, 23 1,009 -> 425, 25 645 -> 470, 100 1,284 -> 927, 255 2,596 -> 1,924;
-// 64 x 65,536, n = 20 34.3 -> 19.6.  Leaves wp.win = 0 when neither applies or
-// the padded window does not fit.
-static void plan_window(const int* W, int n, bool unit, int X, size_t lds_cap, WidthPlan& wp, BoxcarArgs& ba,
-                        int& waves)
+// one array from an offset that is a multiple of 8, where it pays
+// (window_pays).  F32 1,024 x 131,072, lists 1..n, strided -> window: n = 17 547
+// -> 415 us, 25 603 -> 462, 100 1,284 -> 927, 255 2,596 -> 1,924; 64 x 65,536,
+// n = 18 26.3 -> 18.9.  Leaves wp.win = 0 when none applies or the padded
+// window does not fit.
+static void plan_window(const int* W, int n, bool unit, int X, size_t lds_cap, WindowUse use, WidthPlan& wp,
+                        BoxcarArgs& ba, int& waves)
 {
-    if (X != kWinX || !unit) return;
+    if (use == kNoWindow || X != kWinX || !unit) return;
     bool contiguous = n <= 16;
     for (int i = 0; i < n && contiguous; ++i) contiguous = W[i] == i + 1;
     int kind = contiguous ? 2 : 0;
@@ -135,7 +135,7 @@ static void plan_window(const int* W, int n, bool unit, int X, size_t lds_cap, W
     const int ng = (n + kGroup - 1) / kGroup;
     int nread = wp.nmax;
     if (!kind) {
-        kind = 1;
+        kind = use == kAnyWindow || window_pays(n, use == kBatchWindow);
         for (int g = 0; g < ng && kind; ++g) {
             const int i0 = g * kGroup;
             const int o = i0 ? W[i0 - 1] : 0;
@@ -181,7 +181,7 @@ static void plan_window(const int* W, int n, bool unit, int X, size_t lds_cap, W
 
 // Presummed LDS arrays and per-width steps for the boxcar kernel.
 bool build_width_plan(const spd_params* p, int X, WidthPlan& wp, BoxcarArgs& ba, int& waves, size_t lds_reserve,
-                      bool window)
+                      WindowUse window)
 {
     const int n = p->n_widths;
     const int* W = p->widths;
@@ -233,7 +233,7 @@ bool build_width_plan(const spd_params* p, int X, WidthPlan& wp, BoxcarArgs& ba,
     ba.npw = npw;
     ba.wave_floats = wp.n_arr * npw;
     wp.win = 0;
-    if (window) plan_window(W, n, unit, X, lds_cap, wp, ba, waves);
+    plan_window(W, n, unit, X, lds_cap, window, wp, ba, waves);
     return true;
 }
 
@@ -285,8 +285,11 @@ spd_status plan_boxcar(const spd_plane* x, const spd_params* p, const spd_row_st
     const int X = kOutPerLane;
     memset(&bp.ba, 0, sizeof bp.ba);
     bp.waves = 4;
-    const char* form = getenv("SPD_BOXCAR_FORM");          // "strided": never the register-window form
-    const bool window = !(form && strcmp(form, "strided") == 0);
+    // "strided": never the register-window form; "window": wherever it can
+    const char* form = getenv("SPD_BOXCAR_FORM");
+    const WindowUse window = form && strcmp(form, "strided") == 0  ? kNoWindow
+                             : form && strcmp(form, "window") == 0 ? kAnyWindow
+                                                                   : kOneWindow;
     if (!build_width_plan(p, X, bp.wp, bp.ba, bp.waves, 0, window))
         return fail(SPD_E_UNSUPPORTED, "width list does not fit in LDS");
     BoxcarArgs& ba = bp.ba;

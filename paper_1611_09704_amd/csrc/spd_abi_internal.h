@@ -22,8 +22,11 @@ spd_status check_plane(const spd_plane* x, const spd_params* p);
 PlaneArg plane_arg(const spd_plane* x);
 bool plane_vec_ok(const spd_plane* x);
 MsdLayout msd_layout(const spd_plane* x);
+// Whether build_width_plan may choose the register-window form: never, where it pays on one plane or in a batched
+// run (window_pays), or wherever the list allows it.
+enum WindowUse { kNoWindow, kOneWindow, kBatchWindow, kAnyWindow };
 bool build_width_plan(const spd_params* p, int X, WidthPlan& wp, BoxcarArgs& ba, int& waves,
-                      size_t lds_reserve = 0, bool window = false);
+                      size_t lds_reserve = 0, WindowUse window = kNoWindow);
 
 struct BoxcarPlan {
     WidthPlan wp;

@@ -655,7 +655,7 @@ spd_status spd_batch_plan_create(const spd_plane* beams, int32_t n_beams, const 
         P->ba[k].threshold = p->threshold;
     }
     memset(&P->ba[2], 0, sizeof P->ba[2]);
-    if (build_width_plan(&P->params, kWinX, P->wp[2], P->ba[2], P->max_waves[2], kBatchLdsReserve, true) &&
+    if (build_width_plan(&P->params, kWinX, P->wp[2], P->ba[2], P->max_waves[2], kBatchLdsReserve, kBatchWindow) &&
         P->wp[2].win) {
         P->has_win = true;
         P->ba[2].scope = SPD_SCOPE_ROW;

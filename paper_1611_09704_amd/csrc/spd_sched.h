@@ -78,4 +78,13 @@ inline bool schedule_usable(int X, int win, int wgs_per_cu, int grab, bool has_w
 // 871 and 891.  F16, candidates only, 1..8: 192 MB 76 and 69, 400 MB 146 and 149.
 inline bool stream_once(int64_t plane_bytes) { return plane_bytes > (int64_t)256 << 20; }
 
+// Lists of groups of 8 unit-count widths that step by 1 or 2 (the last group may hold fewer) can take the
+// register-window form.  On one plane the strided form keeps a list of up to 16 widths whose last group is short:
+// it has variants that hold all its SNRs in registers and evaluate no more than 8 or 16 widths (F32 1,024 x 131,072,
+// strided and window: 2,4 315 and 446 us; 2,4..20 390 and 495; 1..8,10,12,14 391 and 539; 64 x 65,536, 2,4,6 15.0
+// and 19.8; F16, candidates only, 2,4 213 and 350), and they return NaN where every SNR is NaN, as the window form
+// does not.  From 17 widths on, and in batched runs, whose strided form has no such variants, the window form is the
+// faster one (1..17 547 and 415, 1..16,18,20 655 and 589; batched 2,4,6 on 256 x 65,536 117 and 69).
+inline bool window_pays(int n_widths, bool batched) { return batched || n_widths > 16 || n_widths % 8 == 0; }
+
 }  // namespace spd

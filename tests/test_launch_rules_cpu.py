@@ -30,6 +30,9 @@ int main()
         } else if (!std::strcmp(name, "stream_once")) {
             get(1);
             std::printf("%d\n", (int)spd::stream_once(v[0]));
+        } else if (!std::strcmp(name, "window_pays")) {
+            get(2);
+            std::printf("%d\n", (int)spd::window_pays((int)v[0], v[1] != 0));
         } else {
             return 3;
         }
@@ -93,3 +96,8 @@ def test_stream_shape_covers_every_row_and_fits_a_launch(rule):
 @pytest.mark.parametrize("mb,once", [(32, 0), (128, 0), (192, 0), (256, 0), (320, 1), (400, 1), (2048, 1)])
 def test_stream_loads_past_the_caches_only_from_planes_they_cannot_hold(rule, mb, once):
     assert rule([("stream_once", mb << 20)]) == [(once,)]
+
+
+@pytest.mark.parametrize("n", range(1, 30))
+def test_short_lists_keep_the_strided_form_on_one_plane(rule, n):
+    assert rule([("window_pays", n, 0), ("window_pays", n, 1)]) == [(int(n > 16 or n in (8, 16)),), (1,)]
