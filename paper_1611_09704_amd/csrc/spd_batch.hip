@@ -423,6 +423,14 @@ static std::string tune_cache_path()
     return dir + "/batch_schedule.txt";
 }
 
+// The sources this library was built from: a schedule is only as good as the
+// kernels it was timed with.
+#ifndef SPD_SOURCE_ID
+#define SPD_SOURCE_ID unknown
+#endif
+#define SPD_STR2(x) #x
+#define SPD_STR(x) SPD_STR2(x)
+
 static std::string tune_key(const spd_batch_plan* P)
 {
     hipDeviceProp_t prop;
@@ -430,7 +438,7 @@ static std::string tune_key(const spd_batch_plan* P)
     char buf[256];
     unsigned h = 2166136261u;
     for (int32_t w : P->widths) h = (h ^ (unsigned)w) * 16777619u;
-    snprintf(buf, sizeof buf, "v3|%s|cu%d|dt%d|n%zu|nmax%d|w%08x", prop.gcnArchName, P->cus, P->dtype,
+    snprintf(buf, sizeof buf, "v4|%s|%s|cu%d|dt%d|n%zu|nmax%d|w%08x", SPD_STR(SPD_SOURCE_ID), prop.gcnArchName, P->cus, P->dtype,
              P->widths.size(), P->widths.back(), h);
     return buf;
 }
