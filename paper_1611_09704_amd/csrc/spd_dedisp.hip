@@ -564,12 +564,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
     }
 }
 
-// SPD_DEDISP_FORM=generic selects the chunk-by-chunk kernel for any plan (all
-// kernels give identical sums).
-bool dd_force_generic()
+// SPD_DEDISP_FORM=generic selects the chunk-by-chunk kernel for any plan, "wide"
+// the wide layout wherever it fits (all kernels give identical sums).
+bool dd_forced(const char* form)
 {
     const char* e = getenv("SPD_DEDISP_FORM");
-    return e && strcmp(e, "generic") == 0;
+    return e && strcmp(e, form) == 0;
 }
 
 }  // namespace
@@ -848,12 +848,13 @@ spd_status spd_dedisperse(const spd_dedisp_plan* plan, const spd_plane* fb, floa
     a.groups = plan->groups;
     a.max_delay = plan->max_delay;
     const dim3 grid((uint32_t)(n_dm_tiles * n_t_tiles));
-    if (!dd_force_generic()) {
+    const bool generic = dd_forced("generic");
+    if (!generic && !dd_forced("wide")) {
         const MfShape f = mf_pick(plan, n_out);
         if (f.k >= 0) return device_status(launch_mfma(plan, a, f, (hipStream_t)stream), "de-dispersion launch");
     }
     const size_t wide_lds = (size_t)kDdMaxChunk * plan->groups * 64;
-    if (!dd_force_generic() && kDdMaxChunk * plan->groups <= 64 * kDdWaves * kWideRounds && wide_lds <= kDdLdsMax)
+    if (!generic && kDdMaxChunk * plan->groups <= 64 * kDdWaves * kWideRounds && wide_lds <= kDdLdsMax)
         hipLaunchKernelGGL(dedisp_u8_wide_kernel, grid, dim3(64 * kDdWaves), wide_lds, (hipStream_t)stream, a);
     else
         hipLaunchKernelGGL(dedisp_u8_kernel, grid, dim3(64 * kDdWaves),
