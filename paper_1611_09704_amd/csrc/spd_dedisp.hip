@@ -388,6 +388,7 @@ __host__ __device__ constexpr int mf_copy(int ns) { return (mf_entries(ns, kMfSp
 // apart so that 16 of them use all banks).
 __host__ __device__ constexpr int mf_chan_bytes(int ns) { return 2 * 8 * mf_copy(ns) + 24; }
 __host__ __device__ constexpr int mf_buffer_bytes(int nw, int ns) { return kMfCh * mf_chan_bytes(ns) + nw * 144; }
+constexpr int kMfRows = 4 * 256 * 4;        // a wave's sums on their way out: 256 starts of its 4 trials
 
 // Three dwords of a row from byte g on (a multiple of 4).  Dwords past the last whole one of the row, which only
 // reach starts past the last, repeat it; a row's last, partial dword is read byte by byte.
@@ -544,23 +545,38 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
         cur ^= 1;
     }
 
+    // A lane holds 16 consecutive starts of its trial per 256; through LDS (kMfRows a wave, float4s swizzled so
+    // that neither side conflicts) a store instruction covers 256 consecutive bytes of each of the 4 rows.  Stored
+    // straight from the accumulators, 16 bytes of each of 64 lines an instruction, the sums of few channels were
+    // bound by their stores (128 trials x 262,144 samples, 4 and 16 channels: 62 and 65 us; 32 and 34 like this).
     const int bias = 128 * a.n_chan;
     const int d = d0 + 4 * wv + kb;
-    if (d >= a.n_dm) return;
     float* orow = a.out + (int64_t)d * a.out_stride;
+    float* tr = (float*)(mf_smem + kMfRows * wv) + 256 * kb;
 #pragma unroll
-    for (int k = 0; k < 4 * NS; ++k) {
-        const int64_t t = t0 + 256 * (k >> 2) + 16 * n + 4 * (k & 3);
-        struct __attribute__((aligned(4))) F4 { float v[4]; } f;
+    for (int s = 0; s < NS; ++s) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) f.v[j] = (float)(acc[k][j] + bias);
-        if (t + 3 < a.n_out) {
-            *(F4*)(orow + t) = f;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (t + j < a.n_out) orow[t + j] = f.v[j];
+        for (int q = 0; q < 4; ++q) {
+            const i32x4 v = acc[4 * s + q];
+            *(float4*)(tr + 16 * n + 4 * ((q + (n >> 2)) & 3)) =
+                make_float4((float)(v[0] + bias), (float)(v[1] + bias), (float)(v[2] + bias), (float)(v[3] + bias));
         }
+        wave_sync();
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const float4 w = *(const float4*)(tr + 64 * m + (4 * n & 48) + 4 * ((n + m) & 3));
+            struct __attribute__((aligned(4))) F4 { float v[4]; } f = {{w.x, w.y, w.z, w.w}};
+            const int64_t t = t0 + 256 * s + 64 * m + 4 * n;
+            if (d >= a.n_dm) continue;
+            if (t + 3 < a.n_out) {
+                *(F4*)(orow + t) = f;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (t + j < a.n_out) orow[t + j] = f.v[j];
+            }
+        }
+        wave_sync();
     }
 }
 
@@ -724,7 +740,7 @@ template <int NW, int NS>
 hipError_t launch_mfma_nw(const DedispArgs& a, bool far, uint32_t grid, hipStream_t s)
 {
     const dim3 g(grid), b(64 * NW);
-    const size_t lds = 2 * mf_buffer_bytes(NW, NS);
+    const size_t lds = std::max(2 * mf_buffer_bytes(NW, NS), NW * kMfRows);
     if (far) hipLaunchKernelGGL((dedisp_mfma_kernel<NW, NS, true>), g, b, lds, s, a);
     else hipLaunchKernelGGL((dedisp_mfma_kernel<NW, NS, false>), g, b, lds, s, a);
     return hipGetLastError();
