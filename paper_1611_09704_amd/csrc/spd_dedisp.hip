@@ -376,9 +376,8 @@ typedef const __attribute__((address_space(3))) uint8_t LdsByte;
 typedef const __attribute__((address_space(3))) uint32_t LdsWord;
 typedef const volatile __attribute__((address_space(3))) u32x2 LdsPair;
 
-// A work-group's starts, the 8-byte entries of a copy read when its trials differ by at most `span`, and the
-// entries a copy has room for.
-__host__ __device__ constexpr int mf_starts(int ns) { return 256 * ns; }
+// The 8-byte entries of a copy read when a work-group's trials differ by at most `span`, and the entries a copy has
+// room for.
 __host__ __device__ constexpr int mf_entries(int ns, int span, bool far)
 {
     return ((3 + (far ? 4 : 0) + span) >> 3) + 32 * ns + 1;
@@ -746,25 +745,13 @@ hipError_t launch_mfma_nw(const DedispArgs& a, bool far, uint32_t grid, hipStrea
     return hipGetLastError();
 }
 
-// The matrix form's work-groups: 4 << k waves (16 << k trials) x 256 * ns starts; k = -1: none.
-struct MfShape { int k, ns; };
-
-// 64 trials x 1,024 starts amortise the staging best (4,096 channels x 6,000 trials x 2^17 samples: 28.2 ms
-// against 38.6 with 32 x 512 starts) while they give three quarters of the CUs a work-group (256 channels x 200
-// trials x 50,001 samples, 196 groups: 60 against 72 us); below that smaller groups keep more CUs busy (128
-// channels x 100 trials x 10,000 samples: 20 against 31 us; 512 x 64 x 20,000: 70 against 97).  The 64-trial
-// groups' span limit also sends coarse lists to the smaller ones (512 x 500 x 20,000, 2 samples a trial: 147 us
-// with 32 x 512 starts, 264 in the wide layout).
 MfShape mf_pick(const spd_dedisp_plan* plan, int64_t n_out)
 {
-    auto groups = [&](int k, int ns) {
-        return ((plan->n_dm + (16 << k) - 1) / (16 << k)) * ((n_out + mf_starts(ns) - 1) / mf_starts(ns));
-    };
-    MfShape f{-1, 2};
-    if (plan->mf_span[2] >= 0 && 4 * groups(2, 4) >= 3 * plan->cus) f = {2, 4};
-    else if (plan->mf_span[1] >= 0) f = {1, 2 * groups(1, 4) >= 3 * plan->cus ? 4 : 2};
-    else if (plan->mf_span[0] >= 0) f = {0, 2};
-    if (f.k >= 0 && (uint64_t)groups(f.k, f.ns) * (uint64_t)(256 << f.k) > kMaxGridItems) f.k = -1;
+    const bool fits[3] = {plan->mf_span[0] >= 0, plan->mf_span[1] >= 0, plan->mf_span[2] >= 0};
+    MfShape f = mf_shape(plan->band.n_chan, plan->n_dm, n_out, fits, plan->cus);
+    const int64_t nt = f.k >= 0 ? 16 << f.k : 16;
+    const int64_t groups = ((plan->n_dm + nt - 1) / nt) * ((n_out + mf_starts(f.ns) - 1) / mf_starts(f.ns));
+    if (f.k >= 0 && (uint64_t)groups * (uint64_t)(256 << f.k) > kMaxGridItems) f.k = -1;
     return f;
 }
 

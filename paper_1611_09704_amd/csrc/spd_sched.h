@@ -87,4 +87,32 @@ inline bool stream_once(int64_t plane_bytes) { return plane_bytes > (int64_t)256
 // faster one (1..17 547 and 415, 1..16,18,20 655 and 589; batched 2,4,6 on 256 x 65,536 117 and 69).
 inline bool window_pays(int n_widths, bool batched) { return batched || n_widths > 16 || n_widths % 8 == 0; }
 
+// The matrix form of the de-dispersion: work-groups of 4 << k waves, 16 << k trials x 256 * ns starts each; k = -1:
+// not this form.  fits[k]: the list's delays allow k.  Sizes are channels x trials x starts.
+//
+// 64 trials x 1,024 starts amortise the staging best (4,096 x 6,000 x 2^17: 28.2 ms against 38.6 with 32 x 512
+// starts) while they give three quarters of the CUs a work-group (256 x 200 x 50,001, 196 groups: 60 against 72 us);
+// below that smaller groups keep more CUs busy (128 x 100 x 10,000: 20 against 31 us; 512 x 64 x 20,000: 70 against
+// 97).  Not for 32 trials or fewer, which leave half of their waves without a trial (256 x 32 x 2^20: 149 us with
+// 32 x 1,024 starts, 212 with 64), nor for fewer than 16 channels, whose time goes into the stores, during which a
+// CU's only group of 16 waves has nothing beside it (4 x 128 x 2^18: 31.7 us, 25.7 with 32 x 1,024, 26.5 in the wide
+// layout; 16 x 64 x 2^20: 62, 71 and 80).  Up to 16 trials take groups of 16 where those are 4 a CU or more
+// (256 x 16 x 2^20: 117 us, 153 with 32; 2^18 starts, 2 a CU: 54 and 50).  One channel has nothing to sum
+// (1 x 64 x 2^20: 45 us, 41 in the wide layout).  The 64-trial groups' span limit also sends coarse lists to the
+// smaller ones (512 x 500 x 20,000, 2 samples a trial: 147 us with 32 x 512 starts, 264 in the wide layout).
+struct MfShape { int k, ns; };
+constexpr int mf_starts(int ns) { return 256 * ns; }
+
+inline MfShape mf_shape(int n_chan, int n_dm, int64_t n_out, const bool (&fits)[3], int cus)
+{
+    auto groups = [&](int k, int ns) {
+        return ((n_dm + (16 << k) - 1) / (16 << k)) * ((n_out + mf_starts(ns) - 1) / mf_starts(ns));
+    };
+    if (n_chan < 2) return {-1, 2};
+    if (fits[2] && n_chan >= 16 && n_dm > 32 && 4 * groups(2, 4) >= 3 * cus) return {2, 4};
+    if (fits[0] && n_dm <= 16 && groups(0, 2) >= 4 * cus) return {0, 2};
+    if (fits[1]) return {1, 2 * groups(1, 4) >= 3 * cus ? 4 : 2};
+    return {fits[0] ? 0 : -1, 2};
+}
+
 }  // namespace spd

@@ -33,6 +33,11 @@ int main()
         } else if (!std::strcmp(name, "window_pays")) {
             get(2);
             std::printf("%d\n", (int)spd::window_pays((int)v[0], v[1] != 0));
+        } else if (!std::strcmp(name, "mf_shape")) {
+            get(7);
+            const bool fits[3] = {v[3] != 0, v[4] != 0, v[5] != 0};
+            const spd::MfShape f = spd::mf_shape((int)v[0], (int)v[1], v[2], fits, (int)v[6]);
+            std::printf("%d %d\n", f.k, f.ns);
         } else {
             return 3;
         }
@@ -101,3 +106,17 @@ def test_stream_loads_past_the_caches_only_from_planes_they_cannot_hold(rule, mb
 @pytest.mark.parametrize("n", range(1, 30))
 def test_short_lists_keep_the_strided_form_on_one_plane(rule, n):
     assert rule([("window_pays", n, 0), ("window_pays", n, 1)]) == [(int(n > 16 or n in (8, 16)),), (1,)]
+
+
+@pytest.mark.parametrize("C,n_dm,n_out,fits,shape", [
+    (4096, 6000, 1 << 17, 7, (2, 4)), (256, 200, 50001, 7, (2, 4)), (128, 100, 10000, 7, (1, 2)),
+    (512, 500, 20000, 3, (1, 2)), (33, 36, 900, 1, (0, 2)), (4096, 6000, 1 << 17, 0, (-1, 2)),
+    (256, 33, 1 << 20, 7, (2, 4)), (256, 32, 1 << 20, 7, (1, 4)), (256, 24, 1 << 18, 7, (1, 2)),   # few trials
+    (256, 16, 1 << 20, 7, (0, 2)), (256, 16, 1 << 18, 7, (1, 2)), (256, 17, 1 << 20, 7, (1, 4)),
+    (16, 1, 1024 * 512, 7, (0, 2)), (16, 1, 1023 * 512, 7, (1, 4)),
+    (16, 64, 1 << 20, 7, (2, 4)), (15, 64, 1 << 20, 7, (1, 4)), (2, 64, 1 << 20, 7, (1, 4)),       # few channels
+    (1, 64, 1 << 20, 7, (-1, 2)),
+])
+def test_dedispersion_work_groups(rule, C, n_dm, n_out, fits, shape):
+    got, = rule([("mf_shape", C, n_dm, n_out, fits & 1, fits >> 1 & 1, fits >> 2 & 1, 256)])
+    assert got[0] == shape[0] and (got[0] < 0 or got == shape)
