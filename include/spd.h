@@ -387,8 +387,9 @@ spd_status spd_dedisperse(const spd_dedisp_plan* plan, const spd_plane* fb, floa
  * Batched form: the same path over many beams of uneven shape per step.
  * Every beam gets per-row statistics (Sec. 2.1-2.2), then the boxcar/SNR
  * pass with the fused threshold (Sec. 2.3-2.4); candidates carry their beam
- * index.  One persistent launch covers all beams' MSD blocks and one all
- * their time tiles; both pull work from an atomic queue.
+ * index.  One launch covers all beams' MSD blocks and one all their time
+ * tiles, with one work-group per item or persistent ones that pull tiles from
+ * an atomic queue.
  * ------------------------------------------------------------------------ */
 typedef struct spd_batch_plan spd_batch_plan;
 

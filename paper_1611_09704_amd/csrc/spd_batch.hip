@@ -1,5 +1,5 @@
-// spd_batch.hip -- the detection path over many beams of uneven shape in one
-// persistent launch per step (Sec. 2.1-2.4 applied to every beam).
+// spd_batch.hip -- the detection path over many beams of uneven shape, one
+// launch per step for all of them (Sec. 2.1-2.4 applied to every beam).
 //
 // A plan owns the per-beam descriptors, the block partials, the per-row
 // statistics and a work-queue counter.  A run is three launches:
@@ -16,7 +16,8 @@
 //
 // The autotuner times the boxcar kernel on the plan's own data for a few
 // schedules (outputs per lane, waves per work-group, work-groups per CU) and
-// caches the winner on disk keyed by device, dtype and width list.
+// caches the winner on disk keyed by device, dtype, width list and the sources
+// the library was built from.
 #include <hip/hip_runtime.h>
 
 #include <stdio.h>

@@ -37,7 +37,7 @@ constexpr int kClusterNear = 4;                  // starts each side checked per
 // Grid for the longest lists: as many work-groups as the chip holds at once.
 // The list's length is only known on the device, so every launch has this many
 // (unless the list's capacity is smaller), and each of them takes a run of the
-// list, whose peaks share one atomic.  16,384 work-groups against 2,048: 45 and
+// list; the peaks among a wave's 64 entries share one atomic.  16,384 work-groups against 2,048: 45 and
 // 25 us for 138,000 candidates of 400 pulses (45 before the shared atomic), 510
 // and 131 us for 61,000 peaks among 92,000 candidates (748 before).
 constexpr uint32_t kClusterMaxBlocks = 2048;

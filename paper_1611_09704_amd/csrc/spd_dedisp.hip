@@ -324,7 +324,7 @@ __global__ __launch_bounds__(64 * kDdWaves) void dedisp_u8_wide_kernel(DedispArg
 }
 
 // ---------------------------------------------------------------------------
-// Matrix form (fine DM grids: 4 consecutive trials differ by at most 4 samples)
+// Matrix form (fine DM grids: 4 consecutive trials differ by at most 4 samples, or 9: FAR)
 // ---------------------------------------------------------------------------
 //
 // The sum over channels is a product with 0/1 matrices, which the matrix cores

@@ -1028,7 +1028,8 @@ __device__ void boxcar_tile(const PlaneArg& pl, bool vec, int64_t r, int64_t tt,
     __syncthreads();
 
     const float* lbase = arrs + lane;
-    // output start t = tw + lane + 64 i: per-sample outputs and the fused threshold
+    // output start t = tw + lane + 64 i: per-sample outputs and the fused threshold (one atomic per start index
+    // with candidates)
     auto emit = [&](int i, float m, int idx) {
         const int64_t t = tw + lane + 64 * i;
         const bool valid = t < ba.nout;
@@ -1290,7 +1291,7 @@ __device__ __forceinline__ float4 cvt4(const Loader<DT>& ld, typename RawT<DT>::
 // D[t_i + o + d*j] at m = i + d*j.  The same holds for the list 1..n
 // (n <= 16) over x' itself.  Results are those of boxcar_tile: the same
 // running sums in the same order, and the same first-maximiser rule.
-// UNIT: every group steps by 1 (the lists 1..8k), so no step is chosen per
+// UNIT: every group steps by 1 (the lists 1..n), so no step is chosen per
 // group and the winner's sums are remade from one read per width, not two
 // (74 VGPRs instead of 125: 6 waves per SIMD instead of 4).
 
@@ -1817,7 +1818,7 @@ __device__ __forceinline__ int stream_origin(const BoxcarArgs& ba, int64_t r)
     return ba.snr || ba.widx ? (int)(at & 15) : 0;
 }
 
-// One run of S steps at t_begin whose every start is valid and every sample it
+// One run of S >= 2 steps at t_begin whose every start is valid and every sample it
 // reads (its starts plus the 16 samples after them) lies inside the row.
 // OUT: both outputs are written with 16-byte and 4-byte stores; otherwise
 // candidates only.  Every step is whole, so the stores are unconditional and a
@@ -1854,13 +1855,7 @@ __device__ __forceinline__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, i
         put_shifted(A + lo, cvt4<DT>(ld, s0), mu_hi, mu_lo);
         put_shifted(A + 256 + lo, cvt4<DT>(ld, s1), mu_hi, mu_lo);
     }
-    Raw r0{}, r1{};
-    if (S > 1) {
-        r0 = load(c + kStreamStep);
-        r1 = load(c + kStreamStep + 256);
-    } else if (lane < 4) {
-        r0 = load(c + kStreamStep);
-    }
+    Raw r0 = load(c + kStreamStep), r1 = load(c + kStreamStep + 256);
     if (lane < 4) put_shifted(A + kStreamStep + lo, cvt4<DT>(ld, r0), mu_hi, mu_lo);
     wave_sync();
     for (int k = 0; k < S; ++k) {

@@ -67,7 +67,7 @@ struct WidthPlan {
     int32_t win;            // register-window form: 0 none, 1 groups of 8, 2 the list 1..n (n <= 16),
                             // 3 the decimated search (1..16, then 2^l*(9..16)),
                             // 4 the list 1..n (n <= 16) in the streaming form
-    int32_t win_unit;       // form 1: every group steps by 1 (the lists 1..8k)
+    int32_t win_unit;       // form 1: every group steps by 1 (the lists 1..n)
     uint32_t off[kMaxWidthsPadded];    // element offset of the first read: array base + w_{i-1}
     uint32_t cg[kMaxWidthsPadded];     // cnt | (gap << 16)
     int16_t width[kMaxWidthsPadded];   // w_i

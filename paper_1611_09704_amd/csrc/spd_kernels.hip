@@ -104,8 +104,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SMALLN == 0
 // Boxcars combined with decimation in time: widths 1..16 at every start, and
 // 2^l*(9..16) at starts that are multiples of 2^l, l = 1..levels.  Bound by HBM
 // (9 bytes a start) and the vector units together.  The levels share two LDS
-// regions (23 KB a work-group instead of 30 at four levels) and 80 VGPRs keep 6
-// waves per SIMD instead of 5: 2,048 x 524,288 with statistics 4,091 -> 4,050 us.
+// regions (23 KB a work-group instead of 30 at four levels) and a cap of 80 VGPRs,
+// which spills 2 or 3 of them to scratch, gives 6 waves per SIMD instead of 5: 2,048 x 524,288 with statistics 4,091 -> 4,050 us.
 template <int DT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void boxcar_dit_kernel(PlaneArg pl, bool vec, const spd_row_stats* stats,
                                                          BoxcarArgs ba, WidthPlan wp)
