@@ -34,13 +34,18 @@ namespace {
 constexpr int kClusterWaves = 4;                 // waves per workgroup
 constexpr int kClusterUnroll = 4;                // passes per round
 constexpr int kClusterNear = 4;                  // starts each side checked per lane first
-// Grid for the longest lists: as many work-groups as the chip holds at once.
-// The list's length is only known on the device, so every launch has this many
-// (unless the list's capacity is smaller), and each of them takes a run of the
-// list; the peaks among a wave's 64 entries share one atomic.  16,384 work-groups against 2,048: 45 and
-// 25 us for 138,000 candidates of 400 pulses (45 before the shared atomic), 510
-// and 131 us for 61,000 peaks among 92,000 candidates (748 before).
-constexpr uint32_t kClusterMaxBlocks = 2048;
+// Work-groups: as many as the chip holds at once, each taking a run of the list
+// (or fewer, for a list of small capacity).  The peaks among a wave's 64 entries
+// share one atomic, so short runs are bound by the atomics where most entries
+// are peaks: 16,384, 4,096 and 2,048 work-groups take 396, 202 and 106 us for
+// 32,480 peaks, and 38, 24 and 23 us for 192,000 candidates of 400 pulses.  With
+// windows of many samples, long lists take twice as many, which evens out their
+// runs' unequal work (381,000 candidates of noise, radii 2 and 256: 169, 163 and
+// 187 us; 833,000, radii 32 and 64: 876, 898 and 1,023).  The list's length is
+// only known on the device, so launches with such windows have the larger number
+// and the work-groups that a short list does not need leave at once.
+constexpr uint32_t kClusterBlocks = 2048;
+constexpr int64_t kClusterLong = 262144, kClusterWide = 1024;    // candidates; samples of a window
 
 struct ClusterArgs {
     const float* snr;
@@ -134,13 +139,15 @@ __device__ bool scan_own_row(const ClusterArgs& a, float v, int64_t r, int64_t t
 __global__ __launch_bounds__(64 * kClusterWaves) void cluster_kernel(ClusterArgs a)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t nwaves = (int64_t)gridDim.x * kClusterWaves;
     int64_t n = *a.cand_count;
     if (n > a.cand_capacity) n = a.cand_capacity;
+    const uint32_t blocks = n > kClusterLong ? gridDim.x : min(gridDim.x, kClusterBlocks);
+    if (blockIdx.x >= blocks) return;
+    const int64_t nwaves = (int64_t)blocks * kClusterWaves;
     // Each wave takes a contiguous run of the list, and the runs of one XCD
     // are adjacent: entries appended together lie close together on the
     // plane, so their windows overlap and stay in that XCD's L2.
-    const int64_t wave = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * kClusterWaves + (threadIdx.x >> 6);
+    const int64_t wave = (int64_t)xcd_remap(blockIdx.x, blocks) * kClusterWaves + (threadIdx.x >> 6);
     const int64_t per = (n + nwaves - 1) / nwaves;
     const int64_t i_end = (wave + 1) * per < n ? (wave + 1) * per : n;
     const int64_t i_begin = wave * per;
@@ -237,7 +244,9 @@ spd_status cluster_candidates(const float* snr, int64_t n_rows, int64_t n_out_co
     if (e != hipSuccess) return device_status(e, "count reset launch");
     if (cand_capacity == 0) return SPD_OK;
     const int64_t want = (cand_capacity + kClusterWaves - 1) / kClusterWaves;
-    const uint32_t blocks = want < (int64_t)kClusterMaxBlocks ? (uint32_t)want : kClusterMaxBlocks;
+    const bool wide = (2 * a.dm_radius + 1) * (2 * a.t_radius + 1) >= kClusterWide;
+    const int64_t most = wide && cand_capacity > kClusterLong ? 2 * kClusterBlocks : kClusterBlocks;
+    const uint32_t blocks = (uint32_t)(want < most ? want : most);
     hipLaunchKernelGGL(cluster_kernel, dim3(blocks), dim3(64 * kClusterWaves), 0, s, a);
     return device_status(hipGetLastError(), "cluster launch");
 }
