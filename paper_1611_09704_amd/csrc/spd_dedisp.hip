@@ -579,14 +579,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
     }
 }
 
-// SPD_DEDISP_FORM=generic selects the chunk-by-chunk kernel for any plan, "wide"
-// the wide layout wherever it fits (all kernels give identical sums).
-bool dd_forced(const char* form)
-{
-    const char* e = getenv("SPD_DEDISP_FORM");
-    return e && strcmp(e, form) == 0;
-}
-
 }  // namespace
 }  // namespace spd
 
@@ -851,8 +843,11 @@ spd_status spd_dedisperse(const spd_dedisp_plan* plan, const spd_plane* fb, floa
     a.groups = plan->groups;
     a.max_delay = plan->max_delay;
     const dim3 grid((uint32_t)(n_dm_tiles * n_t_tiles));
-    const bool generic = dd_forced("generic");
-    if (!generic && !dd_forced("wide")) {
+    // SPD_DEDISP_FORM=generic selects the chunk-by-chunk kernel for any plan, "wide" the wide layout wherever it fits
+    // (all kernels give identical sums)
+    const char* form = getenv("SPD_DEDISP_FORM");
+    const bool generic = form && strcmp(form, "generic") == 0, wide = form && strcmp(form, "wide") == 0;
+    if (!generic && !wide) {
         const MfShape f = mf_pick(plan, n_out);
         if (f.k >= 0) return device_status(launch_mfma(plan, a, f, (hipStream_t)stream), "de-dispersion launch");
     }
