@@ -130,11 +130,11 @@ __global__ __launch_bounds__(256) void batch_finalize_kernel(const BeamDesc* bea
     for (int b = threadIdx.x; b < n_beams; b += blockDim.x) starts[b] = beams[b].unit_start;
     __syncthreads();
     const int64_t u = blockIdx.x;
-    if (zero && u == 0 && threadIdx.x == 0) *zero = 0;
     const int b = find_beam(starts, n_beams, u);
     const BeamDesc d = beams[b];
     const int64_t first_item = d.msd_start + (u - d.unit_start) * d.nblk;
     finalize_unit(part + first_item * 6, d.nblk, need_y != 0, false, nullptr, stats + u, nmax, mode, kappa, sh);
+    if (threadIdx.x == 0 && u == 0 && zero) *zero = 0;
 }
 
 // The same where every beam's rows have at most `lanes` blocks: 256 / lanes rows
