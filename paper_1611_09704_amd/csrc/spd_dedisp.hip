@@ -550,32 +550,38 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
     // bound by their stores (128 trials x 262,144 samples, 4 and 16 channels: 62 and 65 us; 32 and 34 like this).
     const int bias = 128 * a.n_chan;
     const int d = d0 + 4 * wv + kb;
-    float* orow = a.out + (int64_t)d * a.out_stride;
+    const bool have = d < a.n_dm, whole = t0 + mf_starts(NS) <= a.n_out;
+    float* orow = a.out + (int64_t)d * a.out_stride + t0 + 4 * n;
     float* tr = (float*)(mf_smem + kMfRows * wv) + 256 * kb;
+    typedef f32x4 RowAny __attribute__((aligned(4)));
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const i32x4 v = acc[4 * s + q];
-            *(float4*)(tr + 16 * n + 4 * ((q + (n >> 2)) & 3)) =
-                make_float4((float)(v[0] + bias), (float)(v[1] + bias), (float)(v[2] + bias), (float)(v[3] + bias));
+            const i32x4 v = acc[4 * s + q] + bias;
+            *(f32x4*)(tr + 16 * n + 4 * ((q + (n >> 2)) & 3)) = __builtin_convertvector(v, f32x4);
         }
         wave_sync();
+        f32x4 w[4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const float4 w = *(const float4*)(tr + 64 * m + (4 * n & 48) + 4 * ((n + m) & 3));
-            struct __attribute__((aligned(4))) F4 { float v[4]; } f = {{w.x, w.y, w.z, w.w}};
-            const int64_t t = t0 + 256 * s + 64 * m + 4 * n;
-            if (d >= a.n_dm) continue;
-            if (t + 3 < a.n_out) {
-                *(F4*)(orow + t) = f;
-            } else {
+        for (int m = 0; m < 4; ++m) w[m] = *(const f32x4*)(tr + 64 * m + (4 * n & 48) + 4 * ((n + m) & 3));
+        wave_sync();
+        if (have && whole) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (t + j < a.n_out) orow[t + j] = f.v[j];
+            for (int m = 0; m < 4; ++m) *(RowAny*)(orow + 256 * s + 64 * m) = w[m];
+        } else if (have) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int64_t left = a.n_out - (t0 + 256 * s + 64 * m + 4 * n);
+                if (left >= 4) {
+                    *(RowAny*)(orow + 256 * s + 64 * m) = w[m];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j)
+                        if (j < left) orow[256 * s + 64 * m + j] = w[m][j];
+                }
             }
         }
-        wave_sync();
     }
 }
 
