@@ -549,22 +549,25 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
     // straight from the accumulators, 16 bytes of each of 64 lines an instruction, the sums of few channels were
     // bound by their stores (128 trials x 262,144 samples, 4 and 16 channels: 62 and 65 us; 32 and 34 like this).
     const int bias = 128 * a.n_chan;
-    const int d = d0 + 4 * wv + kb;
+    // the lane anew: kept from the loop, its parts would take the kernel past 120 VGPRs, and then nothing that runs
+    // beside it finds a register (two served beams: 2% slower, with the other stream's copies waiting)
+    const int me = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)), en = me & 15, ek = me >> 4;
+    const int d = d0 + 4 * wv + ek;
     const bool have = d < a.n_dm, whole = t0 + mf_starts(NS) <= a.n_out;
-    float* orow = a.out + (int64_t)d * a.out_stride + t0 + 4 * n;
-    float* tr = (float*)(mf_smem + kMfRows * wv) + 256 * kb;
+    float* orow = a.out + (int64_t)d * a.out_stride + t0 + 4 * en;
+    float* tr = (float*)(mf_smem + kMfRows * wv) + 256 * ek;
     typedef f32x4 RowAny __attribute__((aligned(4)));
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const i32x4 v = acc[4 * s + q] + bias;
-            *(f32x4*)(tr + 16 * n + 4 * ((q + (n >> 2)) & 3)) = __builtin_convertvector(v, f32x4);
+            *(f32x4*)(tr + 16 * en + 4 * ((q + (en >> 2)) & 3)) = __builtin_convertvector(v, f32x4);
         }
         wave_sync();
         f32x4 w[4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) w[m] = *(const f32x4*)(tr + 64 * m + (4 * n & 48) + 4 * ((n + m) & 3));
+        for (int m = 0; m < 4; ++m) w[m] = *(const f32x4*)(tr + 64 * m + (4 * en & 48) + 4 * ((en + m) & 3));
         wave_sync();
         if (have && whole) {
 #pragma unroll
@@ -572,7 +575,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
         } else if (have) {
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                const int64_t left = a.n_out - (t0 + 256 * s + 64 * m + 4 * n);
+                const int64_t left = a.n_out - (t0 + 256 * s + 64 * m + 4 * en);
                 if (left >= 4) {
                     *(RowAny*)(orow + 256 * s + 64 * m) = w[m];
                 } else {
