@@ -38,9 +38,9 @@ FLOPS_PER_EVAL = 3
 ISSUE_CEILING_T = 256 * 4 * 2 * 64 / 4 * 2.4e9 / 1e12
 
 
-BOXCAR_SOURCES = ("spd_device.h", "spd_kernels.hip", "spd_kernels.h", "spd_internal.h", "spd_stream.hip")
+BOXCAR_SOURCES = ("spd_device.h", "spd_kernels.hip", "spd_kernels.h", "spd_internal.h", "spd_stream.hip", "spd_sched.h")
 CLUSTER_SOURCES = ("spd_cluster.hip",)
-DEDISP_SOURCES = ("spd_dedisp.hip",)
+DEDISP_SOURCES = ("spd_dedisp.hip", "spd_sched.h")
 
 
 def kernel_source_sha(files=BOXCAR_SOURCES) -> str:

@@ -1821,9 +1821,11 @@ __device__ __forceinline__ int stream_origin(const BoxcarArgs& ba, int64_t r)
 // One run of S >= 2 steps at t_begin whose every start is valid and every sample it
 // reads (its starts plus the 16 samples after them) lies inside the row.
 // OUT: both outputs are written with 16-byte and 4-byte stores; otherwise
-// candidates only.  Every step is whole, so the stores are unconditional and a
+// candidates only.  ONCE: samples are loaded past the caches (a variant of its
+// own: the two loads behind a branch cost 0.4% of 2,048 x 524,281, 1..16).
+// Every step is whole, so the stores are unconditional and a
 // step's loads are waited for without waiting for the previous step's stores.
-template <int DT, int N, bool OUT>
+template <int DT, int N, bool OUT, bool ONCE>
 __device__ __forceinline__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, int64_t t_begin, const spd_row_stats& st,
                                                 const BoxcarArgs& ba, const WidthPlan& wp, float* buf)
 {
@@ -1839,14 +1841,7 @@ __device__ __forceinline__ void boxcar_run_fast(const PlaneArg& pl, int64_t r, i
     float* so = OUT ? ba.snr + r * ba.out_stride + t_begin + lo : nullptr;
     uint8_t* wo = OUT ? ba.widx + r * ba.out_stride + t_begin + lo : nullptr;
 
-    const bool once = ba.once != 0;
-    auto load = [&](int64_t at) -> Raw {
-        if (!once) return raw4_any<DT>(ld, at);
-        asm volatile("");                                   // kept apart: merged, both loads would be ordinary
-        const Raw v = raw4_any<DT, true>(ld, at);
-        asm volatile("");
-        return v;
-    };
+    auto load = [&](int64_t at) { return raw4_any<DT, ONCE>(ld, at); };
 
     float* A = buf;
     float* Bv = buf + kStreamBuf;

@@ -104,7 +104,6 @@ struct BoxcarArgs {
     uint32_t out_vec;       // bit 0: snr rows allow 16-byte stores; bit 1: widx rows allow 8-byte stores
     int32_t steps;          // streaming form: steps per run
     int32_t aligned;        // streaming form: steps on the outputs' 64-byte boundaries
-    int32_t once;           // streaming form: samples are loaded past the caches
 };
 
 struct SelectArgs {

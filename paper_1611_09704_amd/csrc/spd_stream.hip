@@ -13,7 +13,7 @@
 
 namespace spd {
 
-template <int DT, int N, bool OUT>
+template <int DT, int N, bool OUT, bool ONCE>
 __global__ __launch_bounds__(256) void boxcar_stream_kernel(PlaneArg pl, const spd_row_stats* stats, BoxcarArgs ba,
                                                             WidthPlan wp)
 {
@@ -29,22 +29,27 @@ __global__ __launch_bounds__(256) void boxcar_stream_kernel(PlaneArg pl, const s
     float* buf = smem + (size_t)wave * 2 * kStreamBuf;
     // OUT: both outputs given and their offsets from a vector boundary agree
     if (t0 >= 0 && t0 + len <= ba.nout && t0 + len + 16 <= pl.n_cols && (OUT || (!ba.snr && !ba.widx)))
-        boxcar_run_fast<DT, N, OUT>(pl, r, t0, st, ba, wp, buf);
+        boxcar_run_fast<DT, N, OUT, ONCE>(pl, r, t0, st, ba, wp, buf);
     else
         boxcar_run_short<DT, N>(pl, r, t0, st, ba, wp, buf);
 }
 
 template <int DT, int N>
 static hipError_t launch_n(const PlaneArg& pl, const spd_row_stats* stats, const BoxcarArgs& ba, const WidthPlan& wp,
-                           bool out, int waves, uint64_t grid, size_t lds, hipStream_t s)
+                           bool out, bool once, int waves, uint64_t grid, size_t lds, hipStream_t s)
 {
     if constexpr (N < 16) {
-        if (wp.n != N) return launch_n<DT, N + 1>(pl, stats, ba, wp, out, waves, grid, lds, s);
+        if (wp.n != N) return launch_n<DT, N + 1>(pl, stats, ba, wp, out, once, waves, grid, lds, s);
     }
-    if (out)
-        hipLaunchKernelGGL((boxcar_stream_kernel<DT, N, true>), dim3(grid), dim3(64 * waves), lds, s, pl, stats, ba, wp);
+    const dim3 g(grid), b(64 * waves);
+    if (out && once)
+        hipLaunchKernelGGL((boxcar_stream_kernel<DT, N, true, true>), g, b, lds, s, pl, stats, ba, wp);
+    else if (out)
+        hipLaunchKernelGGL((boxcar_stream_kernel<DT, N, true, false>), g, b, lds, s, pl, stats, ba, wp);
+    else if (once)
+        hipLaunchKernelGGL((boxcar_stream_kernel<DT, N, false, true>), g, b, lds, s, pl, stats, ba, wp);
     else
-        hipLaunchKernelGGL((boxcar_stream_kernel<DT, N, false>), dim3(grid), dim3(64 * waves), lds, s, pl, stats, ba, wp);
+        hipLaunchKernelGGL((boxcar_stream_kernel<DT, N, false, false>), g, b, lds, s, pl, stats, ba, wp);
     return hipGetLastError();
 }
 
@@ -58,15 +63,15 @@ hipError_t launch_stream(int dtype, const PlaneArg& pl, const spd_row_stats* sta
     BoxcarArgs ba = ba0;
     ba.steps = f.steps;
     ba.aligned = f.aligned;
-    ba.once = stream_once(pl.n_rows * pl.n_cols * (dtype == SPD_F32 ? 4 : dtype == SPD_F16 ? 2 : 1));
+    const bool once = stream_once(pl.n_rows * pl.n_cols * (dtype == SPD_F32 ? 4 : dtype == SPD_F16 ? 2 : 1));
     ba.tiles_per_row = f.tiles_per_row;
     // 16-byte SNR stores and 4-byte width-index stores on one grid of starts
     const bool out = ba.snr && ba.widx && (((uintptr_t)ba.snr / 4 - (uintptr_t)ba.widx) & 3) == 0;
     const uint64_t grid = (uint64_t)pl.n_rows * (uint64_t)ba.tiles_per_row;
     switch (dtype) {
-    case SPD_F32: return launch_n<SPD_F32, 1>(pl, stats, ba, wp, out, waves, grid, lds, s);
-    case SPD_F16: return launch_n<SPD_F16, 1>(pl, stats, ba, wp, out, waves, grid, lds, s);
-    default: return launch_n<SPD_U8, 1>(pl, stats, ba, wp, out, waves, grid, lds, s);
+    case SPD_F32: return launch_n<SPD_F32, 1>(pl, stats, ba, wp, out, once, waves, grid, lds, s);
+    case SPD_F16: return launch_n<SPD_F16, 1>(pl, stats, ba, wp, out, once, waves, grid, lds, s);
+    default: return launch_n<SPD_U8, 1>(pl, stats, ba, wp, out, once, waves, grid, lds, s);
     }
 }
 

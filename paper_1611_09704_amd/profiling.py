@@ -27,9 +27,9 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 COPY_BYTES = 1 << 31          # calibration copy: reads and writes 2 GiB
 WORKLOADS = {"ska": None, "ska16": list(range(1, 17)), "dit": "dit", "cluster": "cluster", "dedisp": "dedisp"}
-BOXCAR_SOURCES = ("spd_device.h", "spd_kernels.hip", "spd_kernels.h", "spd_internal.h", "spd_stream.hip")
+BOXCAR_SOURCES = ("spd_device.h", "spd_kernels.hip", "spd_kernels.h", "spd_internal.h", "spd_stream.hip", "spd_sched.h")
 CLUSTER_SOURCES = ("spd_cluster.hip",)
-DEDISP_SOURCES = ("spd_dedisp.hip",)
+DEDISP_SOURCES = ("spd_dedisp.hip", "spd_sched.h")
 CLUSTER_RADII = (2, 256)     # DM rows, starts
 DIT_LEVELS = 4
 
