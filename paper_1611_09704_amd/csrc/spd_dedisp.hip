@@ -357,7 +357,7 @@ __global__ __launch_bounds__(64 * kDdWaves) void dedisp_u8_wide_kernel(DedispArg
 // FAR (4 consecutive trials up to 9 samples apart): r may reach 15, so A is
 // never moved; every 4 starts take their own read, in the other copy.
 //
-// Measured (4,096 channels x 6,000 trials x 2^17 samples): 28.2 ms, 1.1e14 of the
+// Measured (4,096 channels x 6,000 trials x 2^17 samples): 28.3 ms, 1.1e14 of the
 // definition's additions per second, against 97.6 ms for the wide layout, whose
 // LDS reads and vector adds cover 8 sums an instruction.  The products take
 // about half of it (22.5 cycles each, 1.52e9 of them); the rest is the staging's
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4, 4)))
     // A lane holds 16 consecutive starts of its trial per 256; through LDS (kMfRows a wave, float4s swizzled so
     // that neither side conflicts) a store instruction covers 256 consecutive bytes of each of the 4 rows.  Stored
     // straight from the accumulators, 16 bytes of each of 64 lines an instruction, the sums of few channels were
-    // bound by their stores (128 trials x 262,144 samples, 4 and 16 channels: 62 and 65 us; 32 and 34 like this).
+    // bound by their stores (128 trials x 262,144 samples, 4 and 16 channels: 62 and 65 us; 30 and 31 like this).
     const int bias = 128 * a.n_chan;
     // the lane anew: kept from the loop, its parts would take the kernel past 120 VGPRs, and then nothing that runs
     // beside it finds a register (two served beams: 2% slower, with the other stream's copies waiting)

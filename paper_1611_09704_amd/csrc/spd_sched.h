@@ -90,16 +90,16 @@ inline bool window_pays(int n_widths, bool batched) { return batched || n_widths
 // The matrix form of the de-dispersion: work-groups of 4 << k waves, 16 << k trials x 256 * ns starts each; k = -1:
 // not this form.  fits[k]: the list's delays allow k.  Sizes are channels x trials x starts.
 //
-// 64 trials x 1,024 starts amortise the staging best (4,096 x 6,000 x 2^17: 28.2 ms against 38.6 with 32 x 512
-// starts) while they give three quarters of the CUs a work-group (256 x 200 x 50,001, 196 groups: 60 against 72 us);
-// below that smaller groups keep more CUs busy (128 x 100 x 10,000: 20 against 31 us; 512 x 64 x 20,000: 70 against
-// 97).  Not for 32 trials or fewer, which leave half of their waves without a trial (256 x 32 x 2^20: 149 us with
-// 32 x 1,024 starts, 212 with 64), nor for fewer than 16 channels, whose time goes into the stores, during which a
-// CU's only group of 16 waves has nothing beside it (4 x 128 x 2^18: 31.7 us, 25.7 with 32 x 1,024, 26.5 in the wide
-// layout; 16 x 64 x 2^20: 62, 71 and 80).  Up to 16 trials take groups of 16 where those are 4 a CU or more
-// (256 x 16 x 2^20: 117 us, 153 with 32; 2^18 starts, 2 a CU: 54 and 50).  One channel has nothing to sum
-// (1 x 64 x 2^20: 45 us, 41 in the wide layout).  The 64-trial groups' span limit also sends coarse lists to the
-// smaller ones (512 x 500 x 20,000, 2 samples a trial: 147 us with 32 x 512 starts, 264 in the wide layout).
+// 64 trials x 1,024 starts amortise the staging best (4,096 x 6,000 x 2^17: 28.3-29.6 ms against 39.4 with 32 x 512
+// starts) while they give three quarters of the CUs a work-group (256 x 200 x 50,001, 196 groups: 57 against 68 us);
+// below that smaller groups keep more CUs busy (128 x 100 x 10,000: 19 against 29 us; 512 x 64 x 20,000: 68 against
+// 97).  Not for 32 trials or fewer, which leave half of their waves without a trial (256 x 32 x 2^20: 152 us with
+// 32 x 1,024 starts, 216 with 64), nor for fewer than 16 channels, whose time goes into the stores, during which a
+// CU's only group of 16 waves has nothing beside it (4 x 128 x 2^18: 30.3 us, 25.6 with 32 x 1,024, 26.4 in the wide
+// layout; 16 x 64 x 2^20: 61, 67 and 80).  Up to 16 trials take groups of 16 where those are 4 a CU or more
+// (256 x 16 x 2^20: 117 us, 138 with 32; 2^18 starts, 2 a CU: 51 and 50).  One channel has nothing to sum
+// (1 x 64 x 2^20: 44 us, 41 in the wide layout).  The 64-trial groups' span limit also sends coarse lists to the
+// smaller ones (512 x 500 x 20,000, 2 samples a trial: 145 us with 32 x 512 starts, 263 in the wide layout).
 struct MfShape { int k, ns; };
 constexpr int mf_starts(int ns) { return 256 * ns; }
 
